@@ -7,20 +7,33 @@
 // latent form, which the decode path uses because there only one query row
 // per sequence meets the whole cache.
 //
-// One workgroup of eight waves takes 128 consecutive queries of one
-// (sequence, query head); wave w owns the 16-query block q0 + 16w .. +15 (the
-// code also takes several blocks per wave, which then share every key and
-// value fragment read from LDS; one block per wave with eight waves measured
-// fastest).  Key/value tiles of 64 tokens are staged in LDS (shared by the
-// waves; the next tile's rows are already in registers while the current one
-// is used).  Per tile, wave and query block, on the 16x16x32 fp16 matrix cores:
-//   S^T (64 keys x 16 queries) = K_tile Q_b^T        (contraction over dh)
+// The unit of work is a wave: 32 consecutive queries of one query head.  The
+// units of one (sequence, key/value head) are numbered query block by query
+// block, the G = Hq / Hkv heads of a block next to each other, and a workgroup
+// takes NW consecutive ones: they read the same key/value tiles, and with
+// grouped heads they sit at (nearly) the same positions, so little is computed
+// past the diagonal.  Key/value tiles of 64 tokens are staged in LDS for the
+// workgroup, double-buffered (one barrier per tile): the values, and the keys
+// of layers without rotary embedding, by direct loads that stay in flight
+// while the tile before is used.  Per tile and wave, on the 32x32x16 fp16
+// matrix cores:
+//   S^T (64 keys x 32 queries) = K_tile Q^T          (contraction over dh)
 //   online softmax per query in fp32 (a query is one lane column; its 64
-//   scores sit in that lane and the three lanes l ^ 16, l ^ 32, l ^ 48)
-//   O^T (dh x 16 queries) += V_tile^T P^T            (contraction over keys)
-// (16x16 products keep the accumulators small enough for two waves per SIMD.)
+//   scores sit in that lane and in lane l ^ 32)
+//   O^T (dh x 32 queries) += V_tile^T P^T            (contraction over keys)
 // The query rows stay in registers for the whole kernel.  Keys past a query's
 // position, or past the sequence end, are masked.
+//
+// What bounds it: every key and value fragment is read from LDS once per
+// wave and tile, 256 dh bytes, while the tile's products take 8 dh cycles of
+// the wave's SIMD: with 32 queries per wave the LDS reads of a CU's eight
+// waves (128 bytes per cycle) take as long as their products, with 16 queries
+// twice as long.  The softmax's vector operations come next (32 exponentials
+// and about ten operations per pair of scores and lane: 1.6 times the
+// products' cycles), so the rest is kept few.  Measured against units of 16
+// queries on the 16x16x32 products with one tile buffer: 4 x 640 tokens, 32
+// heads: 38.2 -> 28.5 us; six rotary prompts of 1477 to 2531 tokens, 28 heads
+// over 4: 541 -> 294 us (607 TFLOP/s).
 //
 // Rotary layers (ROPE): a query row is turned once, in registers, at its
 // position within the sequence; a key row is turned while its tile moves from
@@ -28,138 +41,108 @@
 // the angle pos * theta^(-2j/dh)).  The angle is formed in revolutions in
 // fp64 and reduced to [0, 1) there, then sine and cosine come from the
 // hardware's revolution-based instructions in fp32; the turned rows are
-// rounded to fp16 for the matrix cores, like the unturned ones.
+// rounded to fp16 for the matrix cores, like the unturned ones.  A thread
+// turns the same channels of every 64th key, so between the exact angles of
+// every eighth tile it advances (cos, sin) by the fixed angle of 64 positions
+// (four fp32 operations; an fp64 angle with its sine and cosine costs about
+// twenty).
 #include <math.h>
+
+#include <algorithm>
 
 #include "common.h"
 #include "launch.h"
 
 namespace qsvd {
 
-constexpr int kFaQ = 128;       // queries per workgroup
 constexpr int kFaK = 64;        // keys per tile
-constexpr int kFaWaves = 8;
-constexpr int kFaQW = kFaQ / kFaWaves;   // queries per wave
-constexpr int kFaQB = kFaQW / 16;        // 16-query blocks per wave
+constexpr int kFaQW = 32;       // queries per wave
+constexpr int kFaResync = 8;    // tiles between exact key angles
 constexpr float kFaLog2e = 1.4426950408889634f;
 
-template <int DH>
+template <int DH, int NW, int KSP>
 struct FaCfg {
-  static constexpr int KST = DH + 8;       // K tile row stride (halves): 16-byte row reads hit every bank once
-  static constexpr int VST = DH + 16;      // V tile row stride: the transposing reads hit distinct banks
-  static constexpr int OST = DH + 8;       // output staging row stride
-  static constexpr size_t kK = (size_t)kFaK * KST * 2, kV = (size_t)kFaK * VST * 2;
-  static constexpr size_t kOut = (size_t)kFaWaves * kFaQW * OST * 2;
-  static constexpr size_t kLds = kK + kV > kOut ? kK + kV : kOut;
-  static constexpr size_t kLdsRope = kLds + (size_t)(DH / 2) * sizeof(double);   // + revolutions per position of each pair
-  static constexpr int kChunks = kFaK * DH / 8;               // 16-byte runs per K (or V) tile
-  static constexpr int kPerThread = kChunks / (kFaWaves * 64);
-  static_assert(kChunks % (kFaWaves * 64) == 0, "whole runs per thread");
+  static constexpr int UW = NW / KSP;                         // units (query blocks) per workgroup
+  static constexpr int RUNS = DH / 8;                         // 16-byte runs per row
+  static constexpr int OST = DH + 8;                          // output staging row stride (halves)
+  static constexpr int kTile = kFaK * DH * 2;                 // bytes of a K (or V) tile
+  static constexpr int kBuf = 2 * kTile;                      // K then V
+  static constexpr int kOut = UW * kFaQW * OST * 2;
+  static constexpr int kJoin = KSP > 1 ? UW * (64 * 4 * (DH / 2) + 64 * 8) : 0;   // a share's fp32 rows and (m, l)
+  static constexpr size_t kLds = std::max({2 * KSP * kBuf, kOut, kJoin});
+  // + revolutions per position of each pair, then (cos, sin) of its 64-position step
+  static constexpr size_t kLdsRope = kLds + (size_t)(DH / 2) * (sizeof(double) + sizeof(float2));
+  static constexpr int kLPW = kTile / 1024 / UW;              // direct loads per wave and tile of one operand
+  static_assert(kTile % (1024 * UW) == 0 && (KSP == 1 || KSP == 2), "whole 1 KB loads per wave");
 };
 
-// Max and sum over the four 16-lane rows of a wave (lanes l, l ^ 16, l ^ 32,
-// l ^ 48), every lane receiving the result: gfx950's v_permlane32_swap and
-// v_permlane16_swap with both registers holding the value give each lane its
-// partner's value at vector-ALU latency (issued as asm with both registers
-// read-write; the s_nop covers the hazard of a vector write just before).
+// Rotary embedding: none, queries and keys turned in the kernel, or queries
+// only (the keys were turned before).
+enum { FA_PLAIN = 0, FA_ROPE = 1, FA_ROPE_Q = 2 };
+
+// LDS position of 16-byte run c of row `row` in a tile (rows of DH / 8 runs,
+// unpadded, since direct loads write lane after lane): the runs of a row are
+// permuted so that 8 consecutive rows' reads of one run (K), or the 4 rows x
+// 64 bytes of a transposing read (V), fall on distinct banks.
+template <int DH>
+__device__ __forceinline__ int fa_kslot(int row, int c) {
+  return row * (DH / 8) + (c ^ (row & (DH / 8 - 1) & 15));
+}
+template <int DH>
+__device__ __forceinline__ int fa_vslot(int row, int c) {
+  return row * (DH / 8) + (c ^ (DH == 128 ? (row & 3) << 2 : ((row >> 1) & 1) << 2));
+}
+
+// Direct load, 16 bytes per lane: lane p's run at base + off goes to LDS bytes
+// lds + 16 p (`lds` wave-uniform).  Written as asm, so that the compiler does
+// not wait for every load in flight before each transposing LDS read (it
+// cannot tell that they read the other buffer); it has no register outputs,
+// and the s_waitcnt + s_barrier at the head of the tile loop is what completes
+// it.  The s_nop separates the write of M0 from its use.
+__device__ __forceinline__ void fa_direct_load(const _Float16* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
+               : "memory", "m0");
+}
+
+// Both lanes of a pair (l, l ^ 32) get the max / sum of their two values:
+// v_permlane32_swap with both registers holding the value gives each lane its
+// partner's (issued as asm with both registers read-write; the s_nop covers
+// the hazard of a vector write just before).
 __device__ __forceinline__ void fa_swap32(uint32_t& a, uint32_t& b) {
   asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
 }
-__device__ __forceinline__ void fa_swap16(uint32_t& a, uint32_t& b) {
-  asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-}
-__device__ __forceinline__ float fa_rows4_max(float x) {
+__device__ __forceinline__ float fa_pair_max(float x) {
   uint32_t a = __builtin_bit_cast(uint32_t, x), b = a;
   fa_swap32(a, b);
-  uint32_t c = __builtin_bit_cast(uint32_t, fmaxf(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b))), e = c;
-  fa_swap16(c, e);
-  return fmaxf(__builtin_bit_cast(float, c), __builtin_bit_cast(float, e));
+  return fmaxf(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
 }
-__device__ __forceinline__ float fa_rows4_sum(float x) {
+__device__ __forceinline__ float fa_pair_sum(float x) {
   uint32_t a = __builtin_bit_cast(uint32_t, x), b = a;
   fa_swap32(a, b);
-  uint32_t c = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b)), e = c;
-  fa_swap16(c, e);
-  return __builtin_bit_cast(float, c) + __builtin_bit_cast(float, e);
-}
-
-// Rotary staging of a key tile: thread tid turns the 8 pairs of run pc
-// (channels 8 pc .. +7 with their partners dh/2 further) of row tid / PR.
-template <int DH>
-struct FaRope {
-  static constexpr int PR = DH / 16;                     // pair runs per row
-  static constexpr int kActive = kFaK * PR;              // threads with a key row to turn
-  static_assert(kActive <= kFaWaves * 64, "one pair run per thread");
-  static constexpr int KR = FaCfg<DH>::kPerThread > 2 ? FaCfg<DH>::kPerThread : 2;   // key registers per thread
-};
-
-// Key/value tile t of the rows this thread stages (rows past the sequence end
-// re-read its last row; they are masked).  With ROPE the key registers hold
-// the two halves of one pair run instead.
-template <int DH, bool ROPE>
-__device__ __forceinline__ void fa_load_tile(const _Float16* __restrict__ k, const _Float16* __restrict__ v, int tok0,
-                                             int n, int ldkv, int g, int t, int tid,
-                                             i32x4 (&kr)[FaRope<DH>::KR], i32x4 (&vr)[FaCfg<DH>::kPerThread]) {
-  constexpr int RUNS = DH / 8;
-#pragma unroll
-  for (int i = 0; i < FaCfg<DH>::kPerThread; ++i) {
-    const int e = tid + kFaWaves * 64 * i, row = e / RUNS, c8 = e - row * RUNS;
-    const int key = min(t * kFaK + row, n - 1);
-    const int64_t off = (int64_t)(tok0 + key) * ldkv + g * DH + 8 * c8;
-    if (!ROPE) kr[i] = *reinterpret_cast<const i32x4*>(k + off);
-    vr[i] = *reinterpret_cast<const i32x4*>(v + off);
-  }
-  if (ROPE && tid < FaRope<DH>::kActive) {
-    constexpr int PR = FaRope<DH>::PR;
-    const int row = tid / PR, pc = tid - row * PR;
-    const int key = min(t * kFaK + row, n - 1);
-    const _Float16* src = k + (int64_t)(tok0 + key) * ldkv + g * DH + 8 * pc;
-    kr[0] = *reinterpret_cast<const i32x4*>(src);
-    kr[1] = *reinterpret_cast<const i32x4*>(src + DH / 2);
-  }
+  return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
 }
 
 // Turn the rotate-half pairs (a[e], b[e]) of channels j0 + e by the angle
 // pos * theta^(-2j/dh): freq[j] holds theta^(-2j/dh) / (2 pi), so the angle
 // in revolutions is formed and reduced to [0, 1) in fp64 before the fp32
 // sine and cosine.
-__device__ __forceinline__ void fa_rope8(f16x8& a, f16x8& b, int pos, const double* freq) {
+__device__ __forceinline__ void fa_angle(int pos, double freq, float* c, float* s) {
+  double rev = (double)pos * freq;
+  rev -= floor(rev);
+  const float x = (float)rev;
+  *c = __builtin_amdgcn_cosf(x);
+  *s = __builtin_amdgcn_sinf(x);
+}
+__device__ __forceinline__ void fa_turn8(f16x8& a, f16x8& b, const float* c, const float* s) {
   f16x8 ra, rb;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    double rev = (double)pos * freq[e];
-    rev -= floor(rev);
-    const float x = (float)rev;
-    const float c = __builtin_amdgcn_cosf(x), sn = __builtin_amdgcn_sinf(x);
     const float fa = (float)a[e], fb = (float)b[e];
-    ra[e] = (_Float16)(fa * c - fb * sn);
-    rb[e] = (_Float16)(fb * c + fa * sn);
+    ra[e] = (_Float16)fmaf(fa, c[e], -(fb * s[e]));
+    rb[e] = (_Float16)fmaf(fb, c[e], fa * s[e]);
   }
   a = ra;
   b = rb;
-}
-
-// ... and its copy into the LDS tiles (turning the keys of a rotary layer at
-// positions t * 64 + row).
-template <int DH, bool ROPE>
-__device__ __forceinline__ void fa_store_tile(_Float16* ks, _Float16* vs, int tid, int t, const double* freq,
-                                              const i32x4 (&kr)[FaRope<DH>::KR],
-                                              const i32x4 (&vr)[FaCfg<DH>::kPerThread]) {
-  constexpr int RUNS = DH / 8;
-#pragma unroll
-  for (int i = 0; i < FaCfg<DH>::kPerThread; ++i) {
-    const int e = tid + kFaWaves * 64 * i, row = e / RUNS, c8 = e - row * RUNS;
-    if (!ROPE) *reinterpret_cast<i32x4*>(ks + row * FaCfg<DH>::KST + 8 * c8) = kr[i];
-    *reinterpret_cast<i32x4*>(vs + row * FaCfg<DH>::VST + 8 * c8) = vr[i];
-  }
-  if (ROPE && tid < FaRope<DH>::kActive) {
-    constexpr int PR = FaRope<DH>::PR;
-    const int row = tid / PR, pc = tid - row * PR;
-    f16x8 a = __builtin_bit_cast(f16x8, kr[0]), b = __builtin_bit_cast(f16x8, kr[1]);
-    fa_rope8(a, b, t * kFaK + row, freq + 8 * pc);
-    *reinterpret_cast<f16x8*>(ks + row * FaCfg<DH>::KST + 8 * pc) = a;
-    *reinterpret_cast<f16x8*>(ks + row * FaCfg<DH>::KST + 8 * pc + DH / 2) = b;
-  }
 }
 
 // Cache mode: the queries are the last q_len positions of each sequence of a
@@ -170,30 +153,41 @@ struct FaCacheArgs {
   int32_t capacity, q_len, ldkv;
 };
 
-template <int DH, bool ROPE, bool CACHE>
-__global__ void __launch_bounds__(kFaWaves * 64, 2)
+template <int DH, int MODE, bool CACHE, int NW, int KSP>
+__global__ void __launch_bounds__(NW * 64, 2)
 prefill_flash_kernel(const _Float16* __restrict__ q, const _Float16* __restrict__ k, const _Float16* __restrict__ v,
-                     const int32_t* __restrict__ cu, int32_t n_seq, int32_t Hq, int32_t Hkv, int32_t n_qt,
+                     const int32_t* __restrict__ cu, int32_t n_seq, int32_t Hq, int32_t Hkv, int32_t n_wg, int32_t parts,
                      float scale_log2, double log2_theta, FaCacheArgs ca, _Float16* __restrict__ out) {
-  using C = FaCfg<DH>;
-  constexpr int KS = DH / 32;      // contraction steps of the score product
-  constexpr int OB = DH / 16;      // 16-channel blocks of the output
-  constexpr int RUNS = DH / 8;     // 16-byte runs per row
-  extern __shared__ __attribute__((aligned(16))) uint8_t fa_smem[];
-  _Float16* ks = reinterpret_cast<_Float16*>(fa_smem);
-  _Float16* vs = reinterpret_cast<_Float16*>(fa_smem + C::kK);
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int l16 = lane & 15, g = lane >> 4;
+  using C = FaCfg<DH, NW, KSP>;
+  constexpr bool ROPE = MODE == FA_ROPE;
+  static_assert(!ROPE || KSP == 1, "turned keys are shared by the whole workgroup");
+  constexpr int UW = C::UW;
+  constexpr int KS = DH / 16;      // contraction steps of the score product
+  constexpr int OB = DH / 32;      // 32-channel blocks of the output
+  constexpr int RUNS = C::RUNS;
+  extern __shared__ __attribute__((aligned(1024))) uint8_t fa_smem[];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hl = lane >> 5;
 
-  // Workgroup -> (sequence, head, query tile).  The query tiles of one
-  // (sequence, head) read the same key/value rows, so they get ids that one
+  // Workgroup -> (sequence, key/value head, NW units).  The workgroups of one
+  // (sequence, key/value head) read the same rows, so they get ids that one
   // XCD receives (the chip hands workgroup i to XCD i % 8) and share its L2;
-  // within a group the longest tiles (most keys) go first.
-  const int groups = n_seq * Hq, total = groups * n_qt;
-  int lin = blockIdx.x;
-  if (total % 8 == 0) lin = (lin % 8) * (total / 8) + lin / 8;
-  const int grp = lin / n_qt, qt = n_qt - 1 - (lin - grp * n_qt);
-  const int b = grp / Hq, h = grp - b * Hq;
+  // the groups go round the XCDs one by one, so that sequences of different
+  // lengths spread over them, in `parts` interleaved parts each where that
+  // makes a multiple of eight.  Within an XCD, sets of so many parts as make
+  // about 128 workgroups (two rounds of its CUs) run one after the other, the
+  // workgroups with most keys of a set first.
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int wpp = (n_wg + parts - 1) / parts;                   // workgroups per part
+  const int ppx = (n_seq * Hkv * parts + 7) / 8;                // parts per XCD
+  const int per_set = max(1, 128 / wpp);
+  const int set = slot / (per_set * wpp), in_set = slot - set * per_set * wpp;
+  const int n_in = min(per_set, ppx - set * per_set);           // parts of this set
+  const int vg = xcd + 8 * (set * per_set + in_set % n_in);
+  const int grp = vg / parts;
+  const int wg = (wpp - 1 - in_set / n_in) * parts + vg % parts;
+  if (grp >= n_seq * Hkv || wg >= n_wg) return;
+  const int b = grp / Hkv, g_kv = grp - b * Hkv, G = Hq / Hkv;
   // this sequence's rows: query i (i < nq) is row q_row0 + i at position
   // q_off + i, key t (t < nk) is row k_row0 + t at position t; query i sees
   // the keys at positions <= q_off + i
@@ -209,207 +203,393 @@ prefill_flash_kernel(const _Float16* __restrict__ q, const _Float16* __restrict_
     nq = nk = cu[b + 1] - q_row0;
     q_off = 0;
   }
-  const int q0 = qt * kFaQ;
-  if (q0 >= nq) return;
+  const int first = wg * UW / G * kFaQW;                        // first query of the workgroup
+  if (first >= nq) return;
+  // Waves w, w + UW (KSP 2) have the same unit and take every other key tile.
+  const int wu = w % UW, share = w / UW;
+  const int u = wg * UW + wu;                                   // this wave's unit
+  const int qw0 = u / G * kFaQW;                                // its first query
+  const int h = g_kv * G + u % G;                               // its query head
+  const int last_q = min(nq, ((wg + 1) * UW - 1) / G * kFaQW + kFaQW);   // one past the workgroup's last query
+  const int kend = min(nk, q_off + last_q);                     // keys the workgroup can see
+  const int n_tiles = kend > 0 ? (kend + kFaK - 1) / kFaK : 0;
+  const int ldq = Hq * DH, ldkv = CACHE ? ca.ldkv : Hkv * DH;
+  const bool live = qw0 < nq;                                   // the unit has queries
+  const int my_pos = q_off + qw0 + l32;                         // this lane's query position
+  const int wave_last = live ? min(q_off + qw0 + kFaQW - 1, q_off + nq - 1) : -1;
+
   double* freq = reinterpret_cast<double*>(fa_smem + C::kLds);
-  if (ROPE) {
-    if (tid < DH / 2) freq[tid] = exp2(-2.0 * tid / DH * log2_theta) * 0.15915494309189533576888376337251;
+  float2* step = reinterpret_cast<float2*>(freq + DH / 2);
+  if (MODE != FA_PLAIN) {
+    if (tid < DH / 2) {
+      const double f = exp2(-2.0 * tid / DH * log2_theta);
+      freq[tid] = f * 0.15915494309189533576888376337251;
+      if (ROPE) {
+        double rev = (double)kFaK * freq[tid];
+        rev -= floor(rev);
+        float sn, cs;
+        sincosf((float)(rev * 6.283185307179586476925286766559), &sn, &cs);
+        step[tid] = make_float2(cs, sn);
+      }
+    }
     __syncthreads();
   }
-  const int g_kv = (h * Hkv) / Hq;
-  const int ldq = Hq * DH, ldkv = CACHE ? ca.ldkv : Hkv * DH;
-  const int kend = min(nk, q_off + min(nq, q0 + kFaQ));   // keys this tile of queries can see
-  if (CACHE && kend <= 0) {
-    // no query of the tile sees a position (a cache shorter than the query
-    // block): zeros, as for every query without a visible position
-#pragma unroll
-    for (int i = 0; i < kFaQ * RUNS / (kFaWaves * 64); ++i) {
-      const int e = tid + kFaWaves * 64 * i, row = e / RUNS, c8 = e - row * RUNS;
-      if (q0 + row < nq) *reinterpret_cast<f16x8*>(out + (int64_t)(q_row0 + q0 + row) * ldq + h * DH + 8 * c8) = f16x8{};
-    }
-    return;
-  }
-  const int n_tiles = (kend + kFaK - 1) / kFaK;
-  const int qw0 = q0 + kFaQW * w;                   // this wave's first query
-  int my_q[kFaQB];                                  // this lane's query in each block
-#pragma unroll
-  for (int qb = 0; qb < kFaQB; ++qb) my_q[qb] = qw0 + 16 * qb + l16;
 
-  // query slots of the score product: step s, lane group g -> channels 32 s + 8 g .. +7
-  f16x8 qf[kFaQB][KS];
+  // query slots of the score product: step s, lane half hl -> channels 16 s + 8 hl .. +7
+  f16x8 qf[KS];
+  {
+    const int qi = min(qw0 + l32, nq - 1);
+    const _Float16* qrow = q + (int64_t)(q_row0 + qi) * ldq + h * DH + 8 * hl;
 #pragma unroll
-  for (int qb = 0; qb < kFaQB; ++qb) {
-    const _Float16* qrow = q + (int64_t)(q_row0 + min(my_q[qb], nq - 1)) * ldq + h * DH + 8 * g;
+    for (int s = 0; s < KS; ++s) qf[s] = *reinterpret_cast<const f16x8*>(qrow + 16 * s);
+    if (MODE != FA_PLAIN) {                         // slot s pairs with slot s + KS/2 (channels dh/2 further)
 #pragma unroll
-    for (int s = 0; s < KS; ++s) qf[qb][s] = *reinterpret_cast<const f16x8*>(qrow + 32 * s);
-    if (ROPE) {                                     // slot s pairs with slot s + KS/2 (channels dh/2 further)
+      for (int s = 0; s < KS / 2; ++s) {
+        float cs[8], sn[8];
 #pragma unroll
-      for (int s = 0; s < KS / 2; ++s)
-        fa_rope8(qf[qb][s], qf[qb][s + KS / 2], q_off + min(my_q[qb], nq - 1), freq + 32 * s + 8 * g);
+        for (int e = 0; e < 8; ++e) fa_angle(q_off + qi, freq[16 * s + 8 * hl + e], &cs[e], &sn[e]);
+        fa_turn8(qf[s], qf[s + KS / 2], cs, sn);
+      }
     }
   }
 
-  i32x4 kr[FaRope<DH>::KR], vr[C::kPerThread];
-  f32x4 o[kFaQB][OB];
-  float m_run[kFaQB], l_run[kFaQB];
+  // (their wait is here, not in the tile loop, where it would hold up the direct loads)
 #pragma unroll
-  for (int qb = 0; qb < kFaQB; ++qb) {
+  for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(qf[s]));
+
+  // Direct loads of a tile into LDS: load j of this wave fills 1 KB, lane p its
+  // 16 bytes at position 64 * (kLPW wu + j) + p of its share's tile, from the row and
+  // run that belong there.  Rows past the sequence end (only in its last tile)
+  // re-read its last row; they are masked.
+  uint32_t koff[ROPE ? 1 : C::kLPW], voff[C::kLPW];
+  const int p0 = wu * C::kLPW * 64 + lane;
 #pragma unroll
-    for (int ob = 0; ob < OB; ++ob) o[qb][ob] = f32x4{};
-    m_run[qb] = -INFINITY;
-    l_run[qb] = 0.f;
+  for (int j = 0; j < C::kLPW; ++j) {
+    const int row = (p0 + 64 * j) / RUNS, c = (p0 + 64 * j) % RUNS;
+    if (!ROPE) koff[j] = 2u * (uint32_t)(row * ldkv + 8 * (fa_kslot<DH>(row, c) - row * RUNS));
+    voff[j] = 2u * (uint32_t)(row * ldkv + 8 * (fa_vslot<DH>(row, c) - row * RUNS));
   }
+  auto stage = [&](const _Float16* src, const uint32_t* off, int t, uint32_t base) {
+    const _Float16* tile = src + (int64_t)(k_row0 + t * kFaK) * ldkv + g_kv * DH;
+    const uint32_t lds = base + wu * C::kLPW * 1024;
+    if ((t + 1) * kFaK <= nk) {
+#pragma unroll
+      for (int j = 0; j < C::kLPW; ++j) fa_direct_load(tile, off[j], lds + j * 1024);
+    } else {
+#pragma unroll
+      for (int j = 0; j < C::kLPW; ++j) {
+        const int over = max(t * kFaK + (p0 + 64 * j) / RUNS - (nk - 1), 0);
+        fa_direct_load(tile, off[j] - 2u * (uint32_t)(over * ldkv), lds + j * 1024);
+      }
+    }
+  };
+  // Rotary keys: thread tid turns the 8 pairs of run pc (channels 8 pc .. +7
+  // with their partners dh/2 further) of row tid / PR.
+  constexpr int PR = DH / 16;
+  constexpr bool kAllTurn = !ROPE || kFaK * PR == NW * 64;
+  static_assert(!ROPE || kFaK * PR <= NW * 64, "one pair run per thread");
+  const int krow = tid / PR, kpc = tid % PR;
+  i32x4 kr[2];
+  float kc[8], ksn[8];
+  auto load_keys = [&](int t) {
+    if (kAllTurn || krow < kFaK) {
+      const int key = min(t * kFaK + krow, nk - 1);
+      const _Float16* src = k + (int64_t)(k_row0 + key) * ldkv + g_kv * DH + 8 * kpc;
+      kr[0] = *reinterpret_cast<const i32x4*>(src);
+      kr[1] = *reinterpret_cast<const i32x4*>(src + DH / 2);
+    }
+  };
+  auto store_keys = [&](int t, uint8_t* base) {
+    if (kAllTurn || krow < kFaK) {
+      if (t % kFaResync == 0) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) fa_angle(t * kFaK + krow, freq[8 * kpc + e], &kc[e], &ksn[e]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float2 d = step[8 * kpc + e];
+          const float c0 = kc[e];
+          kc[e] = fmaf(c0, d.x, -(ksn[e] * d.y));
+          ksn[e] = fmaf(ksn[e], d.x, c0 * d.y);
+        }
+      }
+      f16x8 a = __builtin_bit_cast(f16x8, kr[0]), bb = __builtin_bit_cast(f16x8, kr[1]);
+      fa_turn8(a, bb, kc, ksn);
+      _Float16* ks = reinterpret_cast<_Float16*>(base);
+      *reinterpret_cast<f16x8*>(ks + 8 * fa_kslot<DH>(krow, kpc)) = a;
+      *reinterpret_cast<f16x8*>(ks + 8 * fa_kslot<DH>(krow, kpc + PR)) = bb;
+    }
+  };
+
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)fa_smem);
+  f32x16 o[OB];
+#pragma unroll
+  for (int ob = 0; ob < OB; ++ob) o[ob] = f32x16{};
+  float m_run = -INFINITY, l_run = 0.f;
   typedef short s16x4 __attribute__((ext_vector_type(4)));
   typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-  fa_load_tile<DH, ROPE>(k, v, k_row0, nk, ldkv, g_kv, 0, tid, kr, vr);
-  for (int t = 0; t < n_tiles; ++t) {
-    __syncthreads();                                // every wave is done with the previous tile
-    fa_store_tile<DH, ROPE>(ks, vs, tid, t, freq, kr, vr);
-    __syncthreads();
-    if (t + 1 < n_tiles) fa_load_tile<DH, ROPE>(k, v, k_row0, nk, ldkv, g_kv, t + 1, tid, kr, vr);
+  // Tile t of the sequence belongs to share t % KSP; round i works on tiles
+  // KSP i .. KSP i + KSP - 1 in buffer i % 2 of each share.
+  const int n_rounds = (n_tiles + KSP - 1) / KSP;
+  auto buffer = [&](int i) { return (KSP * (i & 1) + share) * C::kBuf; };
+  if (share < n_tiles) {
+    if (ROPE) {
+      load_keys(0);
+      store_keys(0, fa_smem);
+    } else {
+      stage(k, koff, share, lds0 + buffer(0));
+    }
+    stage(v, voff, share, lds0 + buffer(0) + C::kTile);
+  }
+  for (int i = 0; i < n_rounds; ++i) {
+    const int t = KSP * i + share;
+    uint8_t* buf = fa_smem + buffer(i);
+    // this round's tiles have landed and every wave is done with the round
+    // before, whose buffers take the next
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    const bool more = t + KSP < n_tiles;
+    if (more) {
+      if (ROPE) load_keys(t + 1);
+      else stage(k, koff, t + KSP, lds0 + buffer(i + 1));
+      stage(v, voff, t + KSP, lds0 + buffer(i + 1) + C::kTile);
+    }
     const int kt0 = t * kFaK;
-    if (kt0 > q_off + qw0 + kFaQW - 1) continue;    // every key of the tile is after this wave's queries
-    // S^T: key block kb, lane (query l16 of block qb, group g) holds keys kt0 + 16 kb + 4 g + v
-    f32x4 sacc[kFaQB][4];
+    if (t < n_tiles && kt0 <= wave_last) {           // else every key of the tile is after this wave's queries
+      const _Float16* ks = reinterpret_cast<const _Float16*>(buf);
+      const _Float16* vs = reinterpret_cast<const _Float16*>(buf + C::kTile);
+      // S^T: key block kb, lane (query l32, half hl) holds keys kt0 + 32 kb + 8 (v / 4) + 4 hl + v % 4.
+      // The key fragments of two contraction steps are read while the two before multiply.
+      f32x16 sacc[2];
+      sacc[0] = sacc[1] = f32x16{};
+      f16x8 kf[2][4];
+      auto read_k = [&](int g) {
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
+        for (int i = 0; i < 4; ++i)
+          kf[g & 1][i] = *reinterpret_cast<const f16x8*>(ks + 8 * fa_kslot<DH>(32 * (i & 1) + l32, 2 * (2 * g + (i >> 1)) + hl));
+      };
+      read_k(0);
 #pragma unroll
-      for (int qb = 0; qb < kFaQB; ++qb) sacc[qb][kb] = f32x4{};
+      for (int g = 0; g < KS / 2; ++g) {
+        if (g + 1 < KS / 2) read_k(g + 1);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        const f16x8 kf = *reinterpret_cast<const f16x8*>(ks + (16 * kb + l16) * C::KST + 32 * s + 8 * g);
+        for (int i = 0; i < 4; ++i)
+          sacc[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[g & 1][i], qf[2 * g + (i >> 1)], sacc[i & 1], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // Value fragments of the 16-key step st: the A operand comes from
+      // transposing reads: lane a of a 16-lane group addresses key base + a/4,
+      // channels 4 (a % 4) .. +3 of the group's 16 channels, and receives
+      // channel a at keys base .. base + 3.
+      f16x8 vf[2][OB];
+      auto read_v = [&](int st) {
+        const int key = 16 * st + 4 * hl + ((lane & 15) >> 2);
 #pragma unroll
-        for (int qb = 0; qb < kFaQB; ++qb)
-          sacc[qb][kb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qf[qb][s], sacc[qb][kb], 0, 0, 0);
+        for (int ob = 0; ob < OB; ++ob) {
+          const int ch = 32 * ob + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+          const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+              (lds_s16x4*)(vs + 8 * fa_vslot<DH>(key, ch >> 3) + (ch & 7)));
+          const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+              (lds_s16x4*)(vs + 8 * fa_vslot<DH>(key + 8, ch >> 3) + (ch & 7)));
+          const f16x4 flo = __builtin_bit_cast(f16x4, lo), fhi = __builtin_bit_cast(f16x4, hi);
+          vf[st & 1][ob] = f16x8{flo[0], flo[1], flo[2], flo[3], fhi[0], fhi[1], fhi[2], fhi[3]};
+        }
+      };
+      read_v(0);                                     // arrives under the softmax
+      // The wait of the scores' first read after the last product, spelled out
+      // before the branch below: the compiler pads one side of it only.
+      asm volatile("s_nop 7\n\ts_nop 7");
+      __builtin_amdgcn_sched_barrier(0);
+      // tiles wholly before this wave's first query and inside the sequence need no mask
+      if (!(kt0 + kFaK - 1 <= q_off + qw0 && kt0 + kFaK <= nk)) {
+        const int lim = min(my_pos, nk - 1) - kt0 - 4 * hl;
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int vv = 0; vv < 16; ++vv)
+            sacc[kb][vv] = 32 * kb + 8 * (vv >> 2) + (vv & 3) <= lim ? sacc[kb][vv] : -INFINITY;
+      }
+      // (v_maximum3: fmaxf would first quiet every product; a NaN score makes
+      // its row NaN either way)
+      float mx = __builtin_elementwise_maximum(sacc[0][0], sacc[1][0]);
+#pragma unroll
+      for (int vv = 1; vv < 16; ++vv)
+        mx = __builtin_elementwise_maximum(mx, __builtin_elementwise_maximum(sacc[0][vv], sacc[1][vv]));
+      const float m_new = fmaxf(m_run, fa_pair_max(mx) * scale_log2);
+      if (__any(m_new != m_run)) {
+        const float alpha = m_new == m_run ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);
+        m_run = m_new;
+        l_run *= alpha;
+#pragma unroll
+        for (int ob = 0; ob < OB; ++ob) o[ob] *= alpha;
+      }
+      // (a query with no visible key yet: every exponential below is exp2(-inf) = 0)
+      const float m_use = m_run == -INFINITY ? 0.f : m_run;
+      float ps[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int vv = 0; vv < 16; ++vv) {
+          sacc[kb][vv] = __builtin_amdgcn_exp2f(fmaf(sacc[kb][vv], scale_log2, -m_use));
+          ps[vv & 3] += sacc[kb][vv];
+        }
+      l_run += fa_pair_sum((ps[0] + ps[1]) + (ps[2] + ps[3]));
+      // O^T += V^T P^T in four 16-key steps: k-slot e of lane half hl is key
+      // 16 st + 8 (e / 4) + 4 hl + e % 4, i.e. score element 8 (st % 2) + e of
+      // key block st / 2.
+#pragma unroll
+      for (int st = 0; st < 4; ++st) {
+        f16x8 pf;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pf[e] = (_Float16)sacc[st >> 1][8 * (st & 1) + e];
+        if (st < 3) read_v(st + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ob = 0; ob < OB; ++ob) o[ob] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[st & 1][ob], pf, o[ob], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-    // softmax per query block; the scores become the probabilities in place
-    // (tiles wholly before this wave's first query and inside the sequence
-    // need no mask)
-    const bool full = kt0 + kFaK - 1 <= q_off + qw0 && kt0 + kFaK <= nk;
-    float p[kFaQB][4][4];
-#pragma unroll
-    for (int qb = 0; qb < kFaQB; ++qb) {
-      float mx = -INFINITY;
-      if (full) {
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-          for (int vv = 0; vv < 4; ++vv) {
-            p[qb][kb][vv] = sacc[qb][kb][vv] * scale_log2;
-            mx = fmaxf(mx, p[qb][kb][vv]);
-          }
-      } else {
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-          for (int vv = 0; vv < 4; ++vv) {
-            const int key = kt0 + 16 * kb + 4 * g + vv;
-            p[qb][kb][vv] = (key <= q_off + my_q[qb] && key < nk) ? sacc[qb][kb][vv] * scale_log2 : -INFINITY;
-            mx = fmaxf(mx, p[qb][kb][vv]);
-          }
-      }
-      const float m_new = fmaxf(m_run[qb], fa_rows4_max(mx));
-      float alpha = 1.f, ps = 0.f;
-      if (m_new == -INFINITY) {
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-          for (int vv = 0; vv < 4; ++vv) p[qb][kb][vv] = 0.f;
-      } else {
-        alpha = __builtin_amdgcn_exp2f(m_run[qb] - m_new);
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-          for (int vv = 0; vv < 4; ++vv) {
-            p[qb][kb][vv] = __builtin_amdgcn_exp2f(p[qb][kb][vv] - m_new);
-            ps += p[qb][kb][vv];
-          }
-      }
-      l_run[qb] = l_run[qb] * alpha + fa_rows4_sum(ps);
-      m_run[qb] = m_new;
-      if (__any(alpha != 1.f)) {
-#pragma unroll
-        for (int ob = 0; ob < OB; ++ob) o[qb][ob] *= alpha;
-      }
-    }
-    // O^T += V^T P^T in two 32-key steps st: k-slot e of lane group g is key
-    // 32 st + 16 (e / 4) + 4 g + e % 4, i.e. score p[2 st + e / 4][e % 4].
-    // The A operand comes from transposing reads: lane a of group g addresses
-    // key 4g + a/4 of the 16-key block, channels 16 ob + 4 (a % 4) .. +3, and
-    // lane i receives element i % 4 of the chunks of lanes i/4, 4 + i/4,
-    // 8 + i/4, 12 + i/4: channel 16 ob + i at keys 4g .. 4g+3 of the block.
-#pragma unroll
-    for (int st = 0; st < 2; ++st) {
-      f16x8 pf[kFaQB];
-#pragma unroll
-      for (int qb = 0; qb < kFaQB; ++qb)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) pf[qb][e] = (_Float16)p[qb][2 * st + (e >> 2)][e & 3];
-      const int key = 32 * st + 4 * g + (l16 >> 2);
-#pragma unroll
-      for (int ob = 0; ob < OB; ++ob) {
-        const _Float16* a0 = vs + key * C::VST + 16 * ob + 4 * (l16 & 3);
-        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)a0);
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(a0 + 16 * C::VST));
-        const f16x4 flo = __builtin_bit_cast(f16x4, lo), fhi = __builtin_bit_cast(f16x4, hi);
-        const f16x8 a = {flo[0], flo[1], flo[2], flo[3], fhi[0], fhi[1], fhi[2], fhi[3]};
-#pragma unroll
-        for (int qb = 0; qb < kFaQB; ++qb) o[qb][ob] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, pf[qb], o[qb][ob], 0, 0, 0);
-      }
-    }
+    if (ROPE && more) store_keys(t + 1, fa_smem + buffer(i + 1));
   }
 
-  // O / l through LDS, so that each query row leaves as 16-byte runs: lane
-  // (l16, g) holds query qw0 + 16 qb + l16 at channels 16 ob + 4 g .. +3.
-  __syncthreads();
-  _Float16* ost = reinterpret_cast<_Float16*>(fa_smem) + w * kFaQW * C::OST;
+  if constexpr (KSP > 1) {
+    // Share 1 leaves its rows, lane by lane, for share 0 of the same unit.
+    __syncthreads();
+    f32x4* jo = reinterpret_cast<f32x4*>(fa_smem) + wu * 64 * (DH / 8);
+    float2* jm = reinterpret_cast<float2*>(fa_smem + UW * 64 * 4 * (DH / 2)) + wu * 64;
+    if (share == 1) {
 #pragma unroll
-  for (int qb = 0; qb < kFaQB; ++qb) {
-    const float inv_l = l_run[qb] > 0.f ? 1.f / l_run[qb] : 0.f;
+      for (int ob = 0; ob < OB; ++ob)
 #pragma unroll
-    for (int ob = 0; ob < OB; ++ob) {
-      const f16x4 v4 = {(_Float16)(o[qb][ob][0] * inv_l), (_Float16)(o[qb][ob][1] * inv_l),
-                        (_Float16)(o[qb][ob][2] * inv_l), (_Float16)(o[qb][ob][3] * inv_l)};
-      *reinterpret_cast<f16x4*>(ost + (16 * qb + l16) * C::OST + 16 * ob + 4 * g) = v4;
+        for (int vq = 0; vq < 4; ++vq)
+          jo[(4 * ob + vq) * 64 + lane] = f32x4{o[ob][4 * vq], o[ob][4 * vq + 1], o[ob][4 * vq + 2], o[ob][4 * vq + 3]};
+      jm[lane] = make_float2(m_run, l_run);
+    }
+    __syncthreads();
+    if (share == 0) {
+      const float2 ml = jm[lane];
+      const float m = fmaxf(m_run, ml.x), mu = m == -INFINITY ? 0.f : m;
+      const float a0 = __builtin_amdgcn_exp2f(m_run - mu), a1 = __builtin_amdgcn_exp2f(ml.x - mu);
+      l_run = l_run * a0 + ml.y * a1;
+#pragma unroll
+      for (int ob = 0; ob < OB; ++ob)
+#pragma unroll
+        for (int vq = 0; vq < 4; ++vq) {
+          const f32x4 x = jo[(4 * ob + vq) * 64 + lane];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[ob][4 * vq + e] = o[ob][4 * vq + e] * a0 + x[e] * a1;
+        }
     }
   }
+  const float inv_l = l_run > 0.f ? 1.f / l_run : 0.f;
+  // O / l through LDS, so that each query row leaves as 16-byte runs: lane
+  // (l32, hl) holds query qw0 + l32 at channels 32 ob + 8 (v / 4) + 4 hl + v % 4.
   __syncthreads();
+  if (!live || share) return;
+  _Float16* ost = reinterpret_cast<_Float16*>(fa_smem) + wu * kFaQW * C::OST;
+#pragma unroll
+  for (int ob = 0; ob < OB; ++ob)
+#pragma unroll
+    for (int vq = 0; vq < 4; ++vq) {
+      const f16x4 v4 = {(_Float16)(o[ob][4 * vq] * inv_l), (_Float16)(o[ob][4 * vq + 1] * inv_l),
+                        (_Float16)(o[ob][4 * vq + 2] * inv_l), (_Float16)(o[ob][4 * vq + 3] * inv_l)};
+      *reinterpret_cast<f16x4*>(ost + l32 * C::OST + 32 * ob + 8 * vq + 4 * hl) = v4;
+    }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the rows below are this wave's own
 #pragma unroll
   for (int i = 0; i < kFaQW * RUNS / 64; ++i) {
     const int e = lane + 64 * i, row = e / RUNS, c8 = e - row * RUNS;
-    const int qq = qw0 + row;
-    if (qq < nq)
-      *reinterpret_cast<f16x8*>(out + (int64_t)(q_row0 + qq) * ldq + h * DH + 8 * c8) =
+    if (qw0 + row < nq)
+      *reinterpret_cast<f16x8*>(out + (int64_t)(q_row0 + qw0 + row) * ldq + h * DH + 8 * c8) =
           *reinterpret_cast<const f16x8*>(ost + row * C::OST + 8 * c8);
   }
 }
 
-template <int DH, bool ROPE, bool CACHE>
+// Workgroups of one (sequence, key/value head): NW units of 32 queries of one
+// of the G heads each.
+static int fa_workgroups(int queries, int G, int nw) {
+  return (int)(((int64_t)((queries + kFaQW - 1) / kFaQW) * G + nw - 1) / nw);
+}
+
+template <int DH, int MODE, bool CACHE, int NW, int KSP>
 static hipError_t launch_flash(const PrefillAttnArgs& a, const FaCacheArgs& ca, hipStream_t s) {
-  using C = FaCfg<DH>;
-  auto kern = prefill_flash_kernel<DH, ROPE, CACHE>;
-  const size_t lds = ROPE ? C::kLdsRope : C::kLds;
+  using C = FaCfg<DH, NW, KSP>;
+  auto kern = prefill_flash_kernel<DH, MODE, CACHE, NW, KSP>;
+  const size_t lds = MODE != FA_PLAIN ? C::kLdsRope : C::kLds;
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  const int n_qt = ((CACHE ? ca.q_len : a.max_seqlen) + kFaQ - 1) / kFaQ;
-  const int64_t blocks = (int64_t)a.batch * a.n_q_heads * n_qt;
-  KernelScope ks(CACHE ? "cache_flash" : ROPE ? "prefill_flash_rope" : "prefill_flash", s);
-  QSVD_LAUNCH(ks, kern, dim3((unsigned)blocks), dim3(kFaWaves * 64), lds, s, a.q, a.k, a.v, a.cu_seqlens, a.batch,
-              a.n_q_heads, a.n_kv_heads, n_qt, a.sm_scale * kFaLog2e, ROPE ? log2((double)a.rope_theta) : 0.0, ca,
-              a.out);
+  const int n_wg = fa_workgroups(CACHE ? ca.q_len : a.max_seqlen, a.n_q_heads / a.n_kv_heads, C::UW);
+  const int64_t groups = (int64_t)a.batch * a.n_kv_heads;
+  int parts = groups % 8 == 0 ? 1 : groups % 4 == 0 ? 2 : groups % 2 == 0 ? 4 : 8;
+  while (parts > n_wg) parts /= 2;
+  const int64_t blocks = (groups * parts + 7) / 8 * 8 * ((n_wg + parts - 1) / parts);
+  KernelScope ks(CACHE ? "cache_flash" : MODE != FA_PLAIN ? "prefill_flash_rope" : "prefill_flash", s);
+  QSVD_LAUNCH(ks, kern, dim3((unsigned)blocks), dim3(NW * 64), lds, s, a.q, a.k, a.v, a.cu_seqlens, a.batch,
+              a.n_q_heads, a.n_kv_heads, n_wg, parts, a.sm_scale * kFaLog2e,
+              MODE != FA_PLAIN ? log2((double)a.rope_theta) : 0.0, ca, a.out);
   return hipGetLastError();
 }
 
 bool prefill_attention_supported(int32_t head_dim) { return head_dim == 64 || head_dim == 128; }
 
+template <int DH>
+static hipError_t launch_prefill(const PrefillAttnArgs& a, hipStream_t s) {
+  const FaCacheArgs none{};
+  // Rotary layers turn the keys once per workgroup, so eight waves take eight
+  // units.  Without that, four: the two workgroups of a CU cover each other's
+  // barriers (four units in two shares of the keys, eight waves: 41 us for the
+  // 4 x 640 prompts, against 28.5).
+  if (a.rope_theta > 0.f) return launch_flash<DH, FA_ROPE, false, 8, 1>(a, none, s);
+  return launch_flash<DH, FA_PLAIN, false, 4, 1>(a, none, s);
+}
+
 hipError_t launch_prefill_attention(const PrefillAttnArgs& a, hipStream_t s) {
   if (a.batch == 0 || a.max_seqlen == 0) return hipSuccess;
-  const FaCacheArgs none{};
-  if (a.rope_theta > 0.f)
-    return a.head_dim == 128 ? launch_flash<128, true, false>(a, none, s) : launch_flash<64, true, false>(a, none, s);
-  return a.head_dim == 128 ? launch_flash<128, false, false>(a, none, s) : launch_flash<64, false, false>(a, none, s);
+  return a.head_dim == 128 ? launch_prefill<128>(a, s) : launch_prefill<64>(a, s);
+}
+
+// Rebuilt keys turned in place at their positions, for layers with rotary
+// embedding: thread (position t, pair run) of a sequence turns that run in
+// every key/value head.  Once per call, where the attention's workgroups (28
+// per sequence and key/value head for 100 queries of 7 heads each) would each
+// turn every key they read.
+template <int DH>
+__global__ void __launch_bounds__(256)
+rope_keys_kernel(_Float16* __restrict__ kv, const int32_t* __restrict__ seq_len, int32_t capacity, int32_t ldkv,
+                 int32_t Hkv, double log2_theta) {
+  constexpr int PR = DH / 16;
+  const int b = blockIdx.y, t = (blockIdx.x * 256 + threadIdx.x) / PR, pc = threadIdx.x % PR;
+  if (t >= min(seq_len[b], capacity)) return;
+  float c[8], sn[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+    fa_angle(t, exp2(-2.0 * (8 * pc + e) / DH * log2_theta) * 0.15915494309189533576888376337251, &c[e], &sn[e]);
+  _Float16* row = kv + ((int64_t)b * capacity + t) * ldkv + 8 * pc;
+  for (int g = 0; g < Hkv; ++g, row += DH) {
+    f16x8 x = *reinterpret_cast<const f16x8*>(row), y = *reinterpret_cast<const f16x8*>(row + DH / 2);
+    fa_turn8(x, y, c, sn);
+    *reinterpret_cast<f16x8*>(row) = x;
+    *reinterpret_cast<f16x8*>(row + DH / 2) = y;
+  }
+}
+
+template <int DH>
+static hipError_t launch_cache(const CacheAttnArgs& c, const PrefillAttnArgs& a, const FaCacheArgs& ca, hipStream_t s) {
+  // Few queries over many keys leave few workgroups: their waves share the
+  // keys in two halves (100 queries of 28 heads over 1899 tokens, 4 sequences:
+  // 87 -> 44 us, and 7 us for turning the keys before).
+  if (c.rope_theta <= 0.f) return launch_flash<DH, FA_PLAIN, true, 8, 2>(a, ca, s);
+  {
+    KernelScope ks("rope_keys", s);
+    const dim3 grid((unsigned)(((int64_t)c.max_len * (DH / 16) + 255) / 256), c.batch);
+    QSVD_LAUNCH(ks, rope_keys_kernel<DH>, grid, dim3(256), 0, s, c.kv, c.seq_len, c.capacity, ca.ldkv, c.n_kv_heads,
+                log2((double)c.rope_theta));
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return launch_flash<DH, FA_ROPE_Q, true, 8, 2>(a, ca, s);
 }
 
 // Queries of several positions per sequence over a cache's rebuilt K^ | V^
@@ -417,12 +597,10 @@ hipError_t launch_prefill_attention(const PrefillAttnArgs& a, hipStream_t s) {
 hipError_t launch_cache_attention(const CacheAttnArgs& c, hipStream_t s) {
   if (c.batch == 0 || c.q_len == 0) return hipSuccess;
   const int nkv = c.n_kv_heads * c.head_dim;
-  PrefillAttnArgs a{c.q, c.kv, c.kv + nkv, nullptr, c.batch, c.q_len, c.n_q_heads, c.n_kv_heads, c.head_dim,
-                    c.sm_scale, c.out, c.rope_theta};
+  const PrefillAttnArgs a{c.q, c.kv, c.kv + nkv, nullptr, c.batch, c.q_len, c.n_q_heads, c.n_kv_heads, c.head_dim,
+                          c.sm_scale, c.out, c.rope_theta};
   const FaCacheArgs ca{c.seq_len, c.capacity, c.q_len, 2 * nkv};
-  if (c.rope_theta > 0.f)
-    return c.head_dim == 128 ? launch_flash<128, true, true>(a, ca, s) : launch_flash<64, true, true>(a, ca, s);
-  return c.head_dim == 128 ? launch_flash<128, false, true>(a, ca, s) : launch_flash<64, false, true>(a, ca, s);
+  return c.head_dim == 128 ? launch_cache<128>(c, a, ca, s) : launch_cache<64>(c, a, ca, s);
 }
 
 }  // namespace qsvd

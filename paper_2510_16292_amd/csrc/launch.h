@@ -164,11 +164,13 @@ hipError_t launch_prefill_attention(const PrefillAttnArgs& a, hipStream_t s);
 
 struct CacheAttnArgs {
   const _Float16* q;        // [batch][q_len][n_q_heads * head_dim]
-  const _Float16* kv;       // rebuilt rows [batch][capacity][2 * n_kv_heads * head_dim]: K^ then V^
+  _Float16* kv;             // rebuilt rows [batch][capacity][2 * n_kv_heads * head_dim]: K^ then V^
+                            // (rotary layers: K^ is turned in place)
   const int32_t* seq_len;   // device [batch]
   int32_t batch, capacity, q_len, n_q_heads, n_kv_heads, head_dim;
   float sm_scale, rope_theta;
   _Float16* out;            // [batch][q_len][n_q_heads * head_dim]
+  int32_t max_len;          // host bound of every seq_len[b]
 };
 hipError_t launch_cache_attention(const CacheAttnArgs& c, hipStream_t s);
 

@@ -621,6 +621,26 @@ def test_prefill_attention_rope_ragged(shape, lengths, theta):
     assert ok, info
 
 
+@pytest.mark.parametrize("theta", [None, 1e4], ids=["plain", "rope"])
+@pytest.mark.parametrize("shape,lengths", [
+    ((3, 1, 64), [31, 32, 33, 63, 64, 65, 1]),   # units of 32 queries and tiles of 64 keys at their edges, one odd group each
+    ((7, 1, 128), [97, 256, 257]),               # seven heads of a group over workgroups of four and eight units
+    ((5, 5, 128), [513, 575]),                   # past the eighth tile (the keys' exact angles are formed anew)
+    ((2, 2, 64), [9] * 70),                      # more (sequence, head) groups than one set of an XCD holds
+], ids=["g3-dh64", "g7-dh128", "mha5-resync", "many-short"])
+def test_prefill_attention_unit_edges(shape, lengths, theta):
+    """Prefill attention where its units (32 queries of a head), key tiles,
+    workgroups and workgroup order have their edges, against the oracle."""
+    hq, hkv, dh = shape
+    Q, K, V = _qkv(380 + hq, sum(lengths), hq, hkv, dh)
+    H.say(f"prefill flash units heads={hq}/{hkv} dh={dh} lengths={lengths[:8]} theta={theta}")
+    out = H.host(H.prefill_attention(H.dev(Q), H.dev(K), H.dev(V), lengths, hq, hkv, dh, rope_theta=theta))
+    want = O.prefill_attention(Q, K, V, lengths, hq, hkv, dh, rope_theta=theta)
+    ok, info = H.close_enough(out, want)
+    H.say(f"  max-abs, rel-L2, rms = {info}")
+    assert ok, info
+
+
 def test_prefill_attention_rope_llava7b_full():
     """The LLaVA-1.5-7B-shaped prompt batch at full size (4 x 640 tokens,
     32 heads x 128, rotary base 10000) in the bench's launch configuration,

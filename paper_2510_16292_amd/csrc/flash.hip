@@ -82,11 +82,11 @@ enum { FA_PLAIN = 0, FA_ROPE = 1, FA_ROPE_Q = 2 };
 
 // LDS position of 16-byte run c of row `row` in a tile (rows of DH / 8 runs,
 // unpadded, since direct loads write lane after lane): the runs of a row are
-// permuted so that 8 consecutive rows' reads of one run (K), or the 4 rows x
+// permuted so that 16 consecutive rows' reads of one run (K), or the 4 rows x
 // 64 bytes of a transposing read (V), fall on distinct banks.
 template <int DH>
 __device__ __forceinline__ int fa_kslot(int row, int c) {
-  return row * (DH / 8) + (c ^ (row & (DH / 8 - 1) & 15));
+  return row * (DH / 8) + (c ^ (DH == 128 ? row & 15 : (row >> 1) & 7));
 }
 template <int DH>
 __device__ __forceinline__ int fa_vslot(int row, int c) {

@@ -51,23 +51,27 @@ __device__ __forceinline__ float dequant(float acc, float rs, float cs) { return
 
 // ---------------------------------------------------------------------------
 // Pipelined kernel: BM x BN output tile per workgroup of 4 or 8 waves (each
-// WM x WN), the contraction in stages of 64 bytes.  With F16 the operands are
-// fp16 (a stage is 32 contraction elements, v_mfma_f32_32x32x16_f16, fp32
+// WM x WN), the contraction in stages of 128 bytes.  With F16 the operands are
+// fp16 (a stage is 64 contraction elements, v_mfma_f32_32x32x16_f16, fp32
 // accumulators; a 16-byte slot is 8 elements, so the slot layout, the loads
 // and the fragment reads are the same) and K counts bytes per row.  Operands go from global
 // memory straight into LDS (global_load_lds_dwordx4: lane i of a wave writes
 // 16 bytes at base + 16 i), NS stages deep, so NS - 1 stages are in flight
 // while one is multiplied; one barrier per stage.
 //
-// LDS layout of a stage: blocks of 16 rows x 64 bytes (1 KB); in a block,
-// 16-byte slot 4 * (row % 16) + (chunk ^ ((row / 4) % 4)) holds contraction
-// chunk `chunk` of that row.  A fragment read (16 consecutive rows, one chunk)
-// then touches every bank once.
+// A stage is one 128-byte cache line of every row: a direct load covers 8
+// rows x 128 bytes.  (Stages of 64 bytes fetch each line from L2 twice, half
+// of it unused each time.)
+//
+// LDS layout of a stage: rows of 128 bytes; 16-byte slot chunk ^ (row / 2 % 8)
+// of a row holds its contraction chunk `chunk`.  A fragment read (16
+// consecutive rows, one chunk) then touches every bank once.
 // ---------------------------------------------------------------------------
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) void glb_void_t;
 
-constexpr int PBK = 64;
+constexpr int PBK = 128;        // contraction bytes per stage
+constexpr int PKK = PBK / 32;   // products' steps per stage
 
 // Wait until at most N direct loads of this wave are outstanding (and its LDS
 // reads are done), then meet the other waves.  Written as one asm statement
@@ -89,7 +93,23 @@ __device__ __forceinline__ void vm_wait_stage(int rem) {
 }
 
 __device__ __forceinline__ int pipe_slot(int row, int chunk) {
-  return (row >> 4) * 1024 + (4 * (row & 15) + (chunk ^ ((row >> 2) & 3))) * 16;
+  return row * PBK + (chunk ^ ((row >> 1) & 7)) * 16;
+}
+
+// Sum over LP = 4, 8 or 16 neighbouring lanes, every lane receiving it: lane
+// exchanges within quads, then between mirrored quads and mirrored halves of
+// a row of 16 (whose lanes already agree).
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float x) {
+  return x + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+template <int LP>
+__device__ __forceinline__ float lanes_sum(float x) {
+  x = dpp_add<0xB1>(x);                       // quad_perm 1 0 3 2
+  x = dpp_add<0x4E>(x);                       // quad_perm 2 3 0 1
+  if constexpr (LP >= 8) x = dpp_add<0x141>(x);   // row_half_mirror
+  if constexpr (LP >= 16) x = dpp_add<0x140>(x);  // row_mirror
+  return x;
 }
 
 template <int BM, int BN, int WM, int WN, int NS>
@@ -97,7 +117,7 @@ struct PipeCfg {
   static constexpr int kWaves = (BM / WM) * (BN / WN);
   static_assert(kWaves == 4 || kWaves == 8, "four or eight waves");
   static constexpr int kThreads = 64 * kWaves;
-  static constexpr int kABlocks = BM / 16, kBBlocks = BN / 16;
+  static constexpr int kABlocks = BM / 8, kBBlocks = BN / 8;
   static_assert((kABlocks + kBBlocks) % kWaves == 0, "whole 1 KB loads per wave");
   static constexpr int kLPW = (kABlocks + kBBlocks) / kWaves;   // direct loads per wave per stage
   static constexpr int kStage = (kABlocks + kBBlocks) * 1024;
@@ -106,7 +126,7 @@ struct PipeCfg {
   static constexpr size_t kLds = kStages > kOut ? kStages : kOut;
 };
 
-template <int BM, int BN, int WM, int WN, int NS, bool DBG, bool F16, bool RS = false>
+template <int BM, int BN, int WM, int WN, int NS, bool DBG, bool F16, int RS = 0>
 __global__ void __launch_bounds__((PipeCfg<BM, BN, WM, WN, NS>::kThreads))
 gemm_i8_pipe_kernel(const int8_t* __restrict__ A, const int8_t* __restrict__ B,
                     const float* __restrict__ rs, const float* __restrict__ cs,
@@ -126,22 +146,25 @@ gemm_i8_pipe_kernel(const int8_t* __restrict__ A, const int8_t* __restrict__ B,
   xcd_tile(blockIdx.x, gridDim.x, n_tiles_n, gm, &tm, &tn);
   const int64_t m0 = (int64_t)tm * BM;
   const int32_t n0 = tn * BN;
-  const int nk = K / PBK;
+  const int nkf = K / PBK, nk = (K + PBK - 1) / PBK;   // whole stages, stages (the last may be half a one)
 
-  // Each direct load of this wave covers one 16-row block of A or B; its
+  // Each direct load of this wave covers one 8-row block of A or B; its
   // per-lane source offset from the tile's first row is fixed, so a stage
-  // only advances the (scalar) tile base by 64 bytes.
+  // only advances the (scalar) tile base by 128 bytes.  In a half stage (K a
+  // multiple of 64 only) the upper half's lanes re-read the lower half.
   const int8_t* a_tile = A + m0 * K;
   const int8_t* b_tile = B + (int64_t)n0 * K;
   uint32_t voff[C::kLPW];
+  // (row / 2 % 8 of lane p's row in block blk is 4 (blk % 2) + p / 16)
+  const int chunk0 = (lane & 7) ^ (lane >> 4);
+  static_assert(C::kLPW % 2 == 0 && C::kABlocks % 2 == 0, "block parity of load j is j's");
 #pragma unroll
   for (int j = 0; j < C::kLPW; ++j) {
     const int blk = w * C::kLPW + j;                         // wave-uniform
     const bool is_a = blk < C::kABlocks;
-    const int row = 16 * (is_a ? blk : blk - C::kABlocks) + (lane >> 2);
-    const int chunk = (lane & 3) ^ ((row >> 2) & 3);
+    const int row = 8 * (is_a ? blk : blk - C::kABlocks) + (lane >> 3);
     const int64_t last = is_a ? M - 1 - m0 : (int64_t)N - 1 - n0;   // clamp ragged tiles to the last row
-    voff[j] = (uint32_t)(min((int64_t)row, last) * K + 16 * chunk);
+    voff[j] = (uint32_t)(min((int64_t)row, last) * K + 16 * (chunk0 ^ (4 * (j & 1))));
   }
   auto issue = [&](int st) {
     uint8_t* base = pipe_smem + (st % NS) * C::kStage;
@@ -149,18 +172,22 @@ gemm_i8_pipe_kernel(const int8_t* __restrict__ A, const int8_t* __restrict__ B,
 #pragma unroll
     for (int j = 0; j < C::kLPW; ++j) {
       const int blk = w * C::kLPW + j;
-      const int8_t* src = (blk < C::kABlocks ? a_tile : b_tile) + k0 + voff[j];
+      const uint32_t back = st < nkf ? 0 : 16 * ((chunk0 ^ (4 * (j & 1))) & 4);
+      const int8_t* src = (blk < C::kABlocks ? a_tile : b_tile) + k0 + (voff[j] - back);
       __builtin_amdgcn_global_load_lds((glb_void_t*)src, (lds_void_t*)(base + blk * 1024), 16, 0, 0);
     }
   };
 
-  // scales first: their wait then leaves the stage loads in flight
-  // (fp16 operands: a NULL scale vector means no scale)
-  for (int i = tid; i < BM; i += C::kThreads) s_rs[i] = (!F16 || rs) ? rs[min(m0 + i, M - 1)] : 1.f;
-  for (int i = tid; i < BN; i += C::kThreads) s_cs[i] = (!F16 || cs) ? cs[min(n0 + i, N - 1)] : 1.f;
+  // Scales first, into a register: their wait then leaves the stage loads in
+  // flight (fp16 operands: a NULL scale vector means no scale).
+  static_assert(BM + BN == C::kThreads, "one scale per thread");
+  const float* sp = tid < BM ? rs : cs;
+  const int64_t si = tid < BM ? min(m0 + tid, M - 1) : (int64_t)min(n0 + tid - BM, N - 1);
+  const float sv = (!F16 || sp) ? sp[si] : 1.f;
 #pragma unroll
   for (int st = 0; st < NS - 1; ++st)
     if (st < nk) issue(st);
+  (tid < BM ? s_rs[tid] : s_cs[tid - BM]) = sv;
 
   Acc acc[TI][TJ];
 #pragma unroll
@@ -168,19 +195,18 @@ gemm_i8_pipe_kernel(const int8_t* __restrict__ A, const int8_t* __restrict__ B,
 #pragma unroll
     for (int j = 0; j < TJ; ++j) acc[i][j] = Acc{};
 
-  // Fragments of one stage, by contraction half kk: af[kk][i], bf[kk][j].
-  // Half 1 of a stage is read while half 0's products run, and half 0 of the
-  // next stage while half 1's products run.
+  // Fragments of one stage, by 32-byte step kk: af[kk % 2][i], bf[kk % 2][j].
+  // Each step is read while the products of the step before run.
   i32x4 af[2][TI], bf[2][TJ];
-  auto read_half = [&](int kt, int kk) {
+  auto read_step = [&](int kt, int kk) {
     const uint8_t* sa = pipe_smem + (kt % NS) * C::kStage;
     const uint8_t* sb = sa + C::kABlocks * 1024;
 #pragma unroll
     for (int i = 0; i < TI; ++i)
-      af[kk][i] = *reinterpret_cast<const i32x4*>(sa + pipe_slot(wm * WM + 32 * i + l32, 2 * kk + hl));
+      af[kk & 1][i] = *reinterpret_cast<const i32x4*>(sa + pipe_slot(wm * WM + 32 * i + l32, 2 * kk + hl));
 #pragma unroll
     for (int j = 0; j < TJ; ++j)
-      bf[kk][j] = *reinterpret_cast<const i32x4*>(sb + pipe_slot(wn * WN + 32 * j + l32, 2 * kk + hl));
+      bf[kk & 1][j] = *reinterpret_cast<const i32x4*>(sb + pipe_slot(wn * WN + 32 * j + l32, 2 * kk + hl));
   };
   auto products = [&](int kk) {
 #pragma unroll
@@ -188,17 +214,17 @@ gemm_i8_pipe_kernel(const int8_t* __restrict__ A, const int8_t* __restrict__ B,
 #pragma unroll
       for (int j = 0; j < TJ; ++j)
         if constexpr (F16)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, bf[kk][j]),
-                                                             __builtin_bit_cast(f16x8, af[kk][i]), acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, bf[kk & 1][j]),
+                                                             __builtin_bit_cast(f16x8, af[kk & 1][i]), acc[i][j], 0, 0, 0);
         else
-          acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bf[kk][j], af[kk][i], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bf[kk & 1][j], af[kk & 1][i], acc[i][j], 0, 0, 0);
   };
 
-  // One MFMA goes out before each LDS read of the other half, so the reads
+  // One MFMA goes out before each LDS read of the next step, so the reads
   // run under the products and every wait the compiler places before a
   // product only covers reads issued before it.
   auto interleave = [&]() {
-    if constexpr (C::kWaves == 8) return;     // two waves per SIMD interleave by themselves
+    if constexpr (C::kWaves == 8) return;     // (its reads go out before all of its products)
 #pragma unroll
     for (int r = 0; r < TI + TJ; ++r) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
@@ -206,29 +232,36 @@ gemm_i8_pipe_kernel(const int8_t* __restrict__ A, const int8_t* __restrict__ B,
     }
     __builtin_amdgcn_sched_group_barrier(0x008, TI * TJ - (TI + TJ), 0);
   };
-  static_assert(TI * TJ >= TI + TJ, "at least as many products as reads per half");
+  static_assert(TI * TJ >= TI + TJ, "at least as many products as reads per step");
 
   // Waiting for stage s (its loads landed; every wave has finished reading
   // stage s - 1) frees slot (s - 1) % NS for stage s + NS - 1.
   vm_wait_stage<C::kLPW, NS - 2>(nk - 1);
   if (NS - 1 < nk) issue(NS - 1);
-  read_half(0, 0);
-  for (int kt = 0; kt < nk; ++kt) {
+  read_step(0, 0);
+  for (int kt = 0; kt < nkf; ++kt) {
+#pragma unroll
+    for (int kk = 0; kk < PKK; ++kk) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (kk == PKK - 1) {
+        // (on the last stage: a full wait and barrier, nothing left to issue)
+        vm_wait_stage<C::kLPW, NS - 2>(nk - 2 - kt);
+        if (kt + NS < nk) issue(kt + NS);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // after the last stage's last step: an unused read of a stage slot,
+      // which keeps this loop free of branches around products
+      read_step(kk == PKK - 1 ? kt + 1 : kt, (kk + 1) % PKK);
+      if (C::kWaves == 8) __builtin_amdgcn_sched_barrier(0);
+      products(kk);
+      interleave();
+    }
     __builtin_amdgcn_sched_barrier(0);
+  }
+  if (nkf < nk) {                                // the half stage
     products(0);
-    read_half(kt, 1);
-    interleave();
-    __builtin_amdgcn_sched_barrier(0);
-    // (on the last stage: a full wait and barrier, nothing left to issue)
-    vm_wait_stage<C::kLPW, NS - 2>(nk - 2 - kt);
-    if (kt + NS < nk) issue(kt + NS);
-    __builtin_amdgcn_sched_barrier(0);
-    // the next stage's first half (after the last stage: an unused read of a
-    // stage slot, which keeps this loop free of branches around products)
+    read_step(nkf, 1);
     products(1);
-    read_half(kt + 1, 0);
-    interleave();
-    __builtin_amdgcn_sched_barrier(0);
   }
 
   // Epilogue.  The integer accumulators are dumped as they are (debug only);
@@ -272,56 +305,71 @@ gemm_i8_pipe_kernel(const int8_t* __restrict__ A, const int8_t* __restrict__ B,
         __builtin_amdgcn_sched_barrier(0);
       }
   }
-  if constexpr (RS) {
-    // Rotary scores of the tile's rows: item (row, head of the tile), the
-    // threads of a wave on consecutive rows of one head.  The staged element
-    // (row, col) sits in the LDS rows of wave (row / WM, col / WN).
+  if constexpr (RS > 0) {
+    // Rotary scores of the tile's rows, RS = head_dim.  A wave takes rows of
+    // the tile, LPR lanes per row with four pairs each: a row's (cos, sin) are
+    // then one contiguous load per lane group (a lane per row read a line of
+    // its own for every 16 bytes: a 65792 x 4096 x 1536 rebuild took 950 us,
+    // 150 of them here, against 892), kept for every head of the tile.  The
+    // staged element (row, col) sits in the LDS rows of wave (row / WM, col / WN).
     __syncthreads();
-    const int dh = re.dh, half = dh >> 1, hpt = BN / dh;
+    constexpr int half = RS / 2, LPR = RS / 8, RPS = 64 / LPR;   // lanes per row, rows per step
+    constexpr int RW = BM / C::kWaves, STEPS = RW / RPS;         // rows of the wave
+    static_assert(RW % RPS == 0 && BN % RS == 0 && half % 4 == 0, "whole steps, whole heads");
+    const int li = lane % LPR, j4 = 4 * li;
+    int row_b[STEPS];                                            // sequence, -1: no score wanted
+    f32x4 tb[STEPS][2];
+    const int row0 = w * RW + lane / LPR;
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+      const int64_t m = m0 + row0 + s * RPS;
+      const int64_t bt = re.row0 + min(m, M - 1);
+      const int b = (int)(bt / re.capacity), t = (int)(bt - (int64_t)b * re.capacity);
+      row_b[s] = m < M && t < min(re.seq_len[b], re.capacity) ? b : -1;
+      const f32x4* src = reinterpret_cast<const f32x4*>(re.rope + (int64_t)(row_b[s] < 0 ? 0 : t) * half + j4);
+      tb[s][0] = src[0];
+      tb[s][1] = src[1];
+    }
     auto staged = [&](int row, int col) {
       const int wv = (row / WM) * (BN / WN) + col / WN;
-      return *reinterpret_cast<const f16x8*>(reinterpret_cast<const _Float16*>(pipe_smem) +
+      return *reinterpret_cast<const f16x4*>(reinterpret_cast<const _Float16*>(pipe_smem) +
                                              (size_t)wv * WM * OST + (row % WM) * OST + col % WN);
     };
-    for (int it = tid; it < BM * hpt; it += C::kThreads) {
-      const int row = it % BM, hl = it / BM;
-      const int64_t m = m0 + row;
-      const int32_t col0 = hl * dh, gkv = (n0 + col0) / dh;
-      if (m >= M || n0 + col0 >= N) continue;
-      const int64_t bt = re.row0 + m;
-      const int b = (int)(bt / re.capacity), t = (int)(bt - (int64_t)b * re.capacity);
-      if (t >= min(re.seq_len[b], re.capacity)) continue;
-      float* prow = re.pre + bt * 32;
-      const float4* cst = reinterpret_cast<const float4*>(re.rope + (int64_t)t * half);
+    for (int col0 = 0; col0 < BN && n0 + col0 < N; col0 += RS) {
+      const int gkv = (n0 + col0) / RS;
       for (int g = 0; g < re.G; ++g) {
-        const float4* qh = reinterpret_cast<const float4*>(re.qrot + ((int64_t)b * re.Hq + gkv * re.G + g) * dh);
-        // rot(k) . q over the pairs (j, j + half):
-        //   cos * (k_j q_j + k'_j q'_j) + sin * (k_j q'_j - k'_j q_j)
-        float acc = 0.f;
-        for (int j0 = 0; j0 < half; j0 += 8) {
-          const f16x8 ka = staged(row, col0 + j0), kb = staged(row, col0 + half + j0);
-          float4 c4[4], qa[2], qb[2];
+        const int h = gkv * re.G + g;
+        int qb_of = -2;                                          // sequence whose query is in qa, qb
+        f32x4 qa = f32x4{}, qb = f32x4{};
 #pragma unroll
-          for (int u = 0; u < 4; ++u) c4[u] = cst[j0 / 2 + u];
-#pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            qa[u] = qh[j0 / 4 + u];
-            qb[u] = qh[(half + j0) / 4 + u];
+        for (int s = 0; s < STEPS; ++s) {
+          if (__any(row_b[s] != qb_of && row_b[s] >= 0)) {
+            qb_of = row_b[s] >= 0 ? row_b[s] : qb_of;
+            const float* qh = re.qrot + ((int64_t)max(qb_of, 0) * re.Hq + h) * RS;
+            qa = *reinterpret_cast<const f32x4*>(qh + j4);
+            qb = *reinterpret_cast<const f32x4*>(qh + half + j4);
           }
+          // rot(k) . q over the lane's pairs (j, j + half):
+          //   cos * (k_j q_j + k'_j q'_j) + sin * (k_j q'_j - k'_j q_j)
+          const int row = row0 + s * RPS;
+          const f16x4 ka = staged(row, col0 + j4), kb = staged(row, col0 + half + j4);
+          float acc = 0.f;
 #pragma unroll
-          for (int i = 0; i < 8; ++i) {
+          for (int i = 0; i < 4; ++i) {
             const float a = (float)ka[i], bb = (float)kb[i];
-            const float qj = qa[i / 4][i % 4], qk = qb[i / 4][i % 4];
-            const float cs_c = (i & 1) ? c4[i / 2].z : c4[i / 2].x, cs_s = (i & 1) ? c4[i / 2].w : c4[i / 2].y;
-            const float uu = fmaf(bb, qk, a * qj), vv = fmaf(-bb, qj, a * qk);
-            acc = fmaf(cs_c, uu, acc);
-            acc = fmaf(cs_s, vv, acc);
+            const float uu = fmaf(bb, qb[i], a * qa[i]), vv = fmaf(-bb, qa[i], a * qb[i]);
+            acc = fmaf(tb[s][i >> 1][2 * (i & 1)], uu, acc);
+            acc = fmaf(tb[s][i >> 1][2 * (i & 1) + 1], vv, acc);
           }
+          acc = lanes_sum<LPR>(acc);
+          if (li == 0 && row_b[s] >= 0) re.pre[(re.row0 + m0 + row) * 32 + h] = acc;
         }
-        prow[gkv * re.G + g] = acc;
       }
-      if (n0 + col0 == 0)
-        for (int h = re.Hq; h < 32; ++h) prow[h] = 0.f;
+      if (gkv == 0)
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s)
+          for (int h = re.Hq + li; h < 32; h += LPR)
+            if (row_b[s] >= 0) re.pre[(re.row0 + m0 + row0 + s * RPS) * 32 + h] = 0.f;
     }
     return;
   }
@@ -364,7 +412,7 @@ static DevSegs to_dev(const GemmArgs& g) {
 // Tiles one XCD runs at once: its 32 CUs, one workgroup each.
 constexpr int kGemmTilesPerXcd = 32;
 
-template <int BM, int BN, int WM, int WN, int NS, bool DBG, bool F16 = false, bool RS = false>
+template <int BM, int BN, int WM, int WN, int NS, bool DBG, bool F16 = false, int RS = 0>
 static hipError_t launch_pipe(const GemmArgs& g, const DevSegs& sg, hipStream_t s, const RopeEpi& re = RopeEpi{}) {
   using C = PipeCfg<BM, BN, WM, WN, NS>;
   auto kern = gemm_i8_pipe_kernel<BM, BN, WM, WN, NS, DBG, F16, RS>;
@@ -381,7 +429,7 @@ static hipError_t launch_pipe(const GemmArgs& g, const DevSegs& sg, hipStream_t 
 
 hipError_t launch_gemm_i8(const GemmArgs& g, hipStream_t s) {
   if (g.M == 0 || g.N == 0) return hipSuccess;
-  if (g.K % PBK) return hipErrorInvalidValue;
+  if (g.K % 64) return hipErrorInvalidValue;
   // outputs are written in 16-byte runs of 8 columns
   for (int i = 0; i < g.n_seg; ++i)
     if (g.seg[i].n0 % 8 || g.seg[i].n % 8 || g.seg[i].ld % 8 || ((uintptr_t)g.seg[i].ptr & 15))
@@ -390,36 +438,45 @@ hipError_t launch_gemm_i8(const GemmArgs& g, hipStream_t s) {
   // 256 x 256 tiles once they fill the chip, 128 x 128 otherwise (and for
   // the accumulator dumps)
   const int64_t big_tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
-  hipError_t e = g.dbg ? launch_pipe<128, 128, 64, 64, 6, true>(g, sg, s)
-                 : big_tiles >= 256 ? launch_pipe<256, 256, 128, 64, 4, false>(g, sg, s)
-                                    : launch_pipe<128, 128, 64, 64, 6, false>(g, sg, s);
+  hipError_t e = g.dbg ? launch_pipe<128, 128, 64, 64, 4, true>(g, sg, s)
+                 : big_tiles >= 256 ? launch_pipe<256, 256, 128, 64, 2, false>(g, sg, s)
+                                    : launch_pipe<128, 128, 64, 64, 4, false>(g, sg, s);
   if (e != hipSuccess || !g.cq) return e;
   return launch_quantize_rows(g.seg[0].ptr, g.M, g.N, g.seg[0].ld, g.abits, 1.f, g.cq, g.sc, s, "latent_quant");
 }
 
 hipError_t launch_gemm_f16(const GemmArgs& g, hipStream_t s) {
   if (g.M == 0 || g.N == 0) return hipSuccess;
-  if (g.K % (PBK / 2) || g.dbg || g.cq) return hipErrorInvalidValue;
+  if (g.K % 32 || g.dbg || g.cq) return hipErrorInvalidValue;
   for (int i = 0; i < g.n_seg; ++i)
     if (g.seg[i].n0 % 8 || g.seg[i].n % 8 || g.seg[i].ld % 8 || ((uintptr_t)g.seg[i].ptr & 15))
       return hipErrorInvalidValue;
   const DevSegs sg = to_dev(g);
   const int64_t big_tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
-  return big_tiles >= 256 ? launch_pipe<256, 256, 128, 64, 4, false, true>(g, sg, s)
-                          : launch_pipe<128, 128, 64, 64, 6, false, true>(g, sg, s);
+  return big_tiles >= 256 ? launch_pipe<256, 256, 128, 64, 2, false, true>(g, sg, s)
+                          : launch_pipe<128, 128, 64, 64, 4, false, true>(g, sg, s);
+}
+
+template <int DH>
+static hipError_t launch_rope_scores(const GemmArgs& g, const DevSegs& sg, hipStream_t s, const RopeEpi& re, bool f16,
+                                     bool big) {
+  if (f16)
+    return big ? launch_pipe<256, 256, 128, 64, 2, false, true, DH>(g, sg, s, re)
+               : launch_pipe<128, 128, 64, 64, 4, false, true, DH>(g, sg, s, re);
+  return big ? launch_pipe<256, 256, 128, 64, 2, false, false, DH>(g, sg, s, re)
+             : launch_pipe<128, 128, 64, 64, 4, false, false, DH>(g, sg, s, re);
 }
 
 hipError_t launch_gemm_rope_scores(const GemmArgs& g, const RopeEpi& re, bool f16, hipStream_t s) {
   if (g.M == 0 || g.N == 0) return hipSuccess;
-  if ((f16 ? g.K % (PBK / 2) : g.K % PBK) || g.dbg || g.cq) return hipErrorInvalidValue;
+  if ((f16 ? g.K % 32 : g.K % 64) || g.dbg || g.cq) return hipErrorInvalidValue;
   if (re.dh < 32 || 128 % re.dh || g.N % re.dh || re.Hq > 32 || re.G < 1) return hipErrorInvalidValue;
   const DevSegs sg{};
   const int64_t big_tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
-  if (f16)
-    return big_tiles >= 256 ? launch_pipe<256, 256, 128, 64, 4, false, true, true>(g, sg, s, re)
-                            : launch_pipe<128, 128, 64, 64, 6, false, true, true>(g, sg, s, re);
-  return big_tiles >= 256 ? launch_pipe<256, 256, 128, 64, 4, false, false, true>(g, sg, s, re)
-                          : launch_pipe<128, 128, 64, 64, 6, false, false, true>(g, sg, s, re);
+  const bool big = big_tiles >= 256;
+  return re.dh == 32   ? launch_rope_scores<32>(g, sg, s, re, f16, big)
+         : re.dh == 64 ? launch_rope_scores<64>(g, sg, s, re, f16, big)
+                       : launch_rope_scores<128>(g, sg, s, re, f16, big);
 }
 
 }  // namespace qsvd

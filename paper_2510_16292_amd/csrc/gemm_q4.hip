@@ -3,15 +3,24 @@
 // Section 4's per-group int4 weights).
 //
 // Same pipeline as the int8 kernel (operands global -> LDS with
-// global_load_lds_dwordx4, NS stages of 64 contraction elements, one barrier
-// per stage) on 128 x 128 tiles of four 64 x 64 waves.  A stage row holds 64
-// codes: 64 bytes (int8) or 32 bytes (int4, element 2i in the low nibble of
-// byte i); int4 fragments are read 8 bytes at a time and widened in registers
-// to int8 bytes holding 16 * code before v_mfma_i32_32x32x32_i8, so every
-// product is exact and the int32 sums are exact multiples of 16 or 256.
+// global_load_lds_dwordx4, NS stages of 128 contraction elements, one barrier
+// per stage) on 128 x 128 tiles of four 64 x 64 waves, two workgroups per CU.
+// A stage row holds 128 codes: 128 bytes (int8) or 64 bytes (int4, element 2i
+// in the low nibble of byte i).  A lane takes 32 codes of a row at once (one
+// 16-byte read of an int4 row, two of an int8 row), the A and the B lanes the
+// same ones; int4 codes are widened in registers to int8 bytes holding
+// 16 * code before v_mfma_i32_32x32x32_i8, so every product is exact and the
+// int32 sums are exact multiples of 16 or 256.
+//
+// What bounds it: the vector operations of a group of 128 per 32 x 32 tile,
+// 48 for the fold below and 24 for the widening, take 288 cycles where its
+// products take 128.  So the fold is kept to its three operations (the
+// products of a group start from a literal zero, the accumulators stay in
+// vector registers) and runs tile by tile between the next group's first
+// products.  W4A4, 5632 x 15360 x 2048: 382 -> 288 us.
 //
 // Per-group scales (groups of G contraction elements, G a multiple of 64):
-// at the end of each group the int32 tile is folded into an fp32 tile as
+// after each group the int32 tile is folded into an fp32 tile as
 // S = S + f32(acc_g) * s[g][n] (each product and sum rounded to fp32, groups
 // in order) and the int32 tile restarts from zero; the output is S * s_row.
 // Per-channel scales: (f32(acc) * s_row) * s_col.  Both are the definition's
@@ -24,7 +33,7 @@ namespace qsvd {
 typedef __attribute__((address_space(3))) void q4_lds_void_t;
 typedef __attribute__((address_space(1))) void q4_glb_void_t;
 
-constexpr int QBM = 128, QBN = 128, QWM = 64, QWN = 64, QNS = 6, QBK = 64;
+constexpr int QBM = 128, QBN = 128, QWM = 64, QWN = 64, QBK = 128;
 
 template <int N>
 __device__ __forceinline__ void q4_wait_barrier() {
@@ -41,13 +50,12 @@ __device__ __forceinline__ void q4_wait_stage(int rem) {
   }
 }
 
-// LDS slot of (row, 16-byte chunk) in an operand tile whose rows are RB bytes
-// (64: four chunks, 32: two).  The XOR keeps the rows of one fragment read
-// (16 consecutive rows, same chunk) on distinct banks.
+// LDS position of 16-byte chunk `chunk` of a row in an operand tile whose rows
+// are RB bytes (128: eight chunks, 64: four).  The XOR keeps the rows of one
+// fragment read (16 consecutive rows, same chunk) on distinct banks.
 template <int RB>
-__device__ __forceinline__ int q4_slot(int row, int chunk) {
-  if constexpr (RB == 64) return row * 64 + 16 * (chunk ^ ((row >> 2) & 3));
-  else return row * 32 + 16 * (chunk ^ ((row >> 3) & 1));
+__device__ __forceinline__ int q4_swz(int row, int chunk) {
+  return RB == 128 ? chunk ^ ((row >> 1) & 7) : chunk ^ ((row >> 2) & 3);
 }
 
 // 16 int4 codes (8 bytes, element 2i in the low nibble of byte i) -> 16 int8
@@ -69,18 +77,30 @@ __device__ __forceinline__ i32x4 q4_interleave(i32x4 v) {
                (int32_t)__builtin_amdgcn_perm((uint32_t)v[3], (uint32_t)v[2], 0x07050301u)};
 }
 
-// Fragment for sub-step kk (32 contraction elements) of a 32x32x32 MFMA: lane
-// (row, hl) supplies elements 32*kk + 16*hl .. +15 of its row, in natural
-// order when both operands are int8, else in q4_widen's order (the same
-// order in both operands, so the sum runs over the same products).
+// The 32 codes of lane (row, hl) in half h of a stage (elements 64 h + 32 hl
+// .. +31): as read from LDS, and as the fragments of its two 16-code steps, in
+// natural order when both operands are int8, else in q4_widen's order (the
+// same order in both operands, so the sum runs over the same products).
+template <int BITS>
+struct Q4Raw {
+  i32x4 r[BITS / 4];
+};
+template <int BITS>
+__device__ __forceinline__ Q4Raw<BITS> q4_read(const uint8_t* base, int row, int h, int hl) {
+  constexpr int RB = QBK * BITS / 8;
+  Q4Raw<BITS> o;
+#pragma unroll
+  for (int i = 0; i < BITS / 4; ++i)
+    o.r[i] = *reinterpret_cast<const i32x4*>(base + row * RB + 16 * q4_swz<RB>(row, (BITS / 4) * (2 * h + hl) + i));
+  return o;
+}
 template <int BITS, int OTHER>
-__device__ __forceinline__ i32x4 q4_frag(const uint8_t* base, int row, int kk, int hl) {
+__device__ __forceinline__ i32x4 q4_step(const Q4Raw<BITS>& w, int kk) {
   if constexpr (BITS == 8) {
-    const i32x4 v = *reinterpret_cast<const i32x4*>(base + q4_slot<64>(row, 2 * kk + hl));
-    if constexpr (OTHER == 8) return v;
-    else return q4_interleave(v);
+    if constexpr (OTHER == 8) return w.r[kk];
+    else return q4_interleave(w.r[kk]);
   } else {
-    return q4_widen(*reinterpret_cast<const uint2*>(base + q4_slot<32>(row, kk) + 8 * hl));
+    return q4_widen(make_uint2((uint32_t)w.r[0][2 * kk], (uint32_t)w.r[0][2 * kk + 1]));
   }
 }
 
@@ -97,15 +117,33 @@ __device__ __forceinline__ _Float16* q4_col(const Q4Segs& sg, int32_t n, int64_t
   return base ? base + (n - (in0 ? sg.a0 : in1 ? sg.a1 : sg.a2)) : nullptr;
 }
 
-template <int ABITS, int BBITS, bool GROUPED>
-__global__ void __launch_bounds__(256)
+// Scale groups: none (one scale per channel), 128 elements (a stage each), or
+// any other multiple of 64.
+enum { Q4_CHANNEL = 0, Q4_G128 = 1, Q4_GROUP = 2 };
+
+template <int ABITS, int BBITS, int GM>
+struct Q4Cfg {
+  static constexpr int RBA = QBK * ABITS / 8, RBB = QBK * BBITS / 8;   // stage row bytes
+  static constexpr int SA = QBM * RBA, SB = QBN * RBB;
+  static constexpr int kScaleRows = GM;                                // scale rows per stage: 0, 1 or 2
+  static constexpr int kStage = SA + SB + kScaleRows * QBN * 2 * 4;    // each of the four waves has its 64 columns' scales
+  static constexpr int LPW = (SA + SB) / 4096;                         // 16-byte direct loads per wave per stage
+  static constexpr int NS = SA + SB <= 16384 ? 4 : SA + SB <= 24576 ? 3 : 2;
+  static constexpr int kOut = 4 * QWM * (QWN + 8) * 2;
+  static constexpr size_t kLds = NS * kStage > kOut ? NS * kStage : kOut;
+  static_assert(2 * (kLds + 1024) <= 160 * 1024, "two workgroups per CU");
+  static_assert(LPW % 2 == 0 && SA % 2048 == 0, "block parity of load j is j's");
+};
+
+template <int ABITS, int BBITS, int GM>
+__global__ void __launch_bounds__(256, 2)
 gemm_q4_pipe_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B,
                     const float* __restrict__ rs, const float* __restrict__ cs, int32_t sstride,
                     int64_t M, int32_t N, int32_t K, int32_t group, int32_t n_tiles_n, int32_t gm, Q4Segs sg) {
-  constexpr int RBA = QBK * ABITS / 8, RBB = QBK * BBITS / 8;        // stage row bytes
-  constexpr int SA = QBM * RBA, SB = QBN * RBB, STAGE = SA + SB;
-  constexpr int LPW = STAGE / 1024 / 4;                               // direct loads per wave per stage
-  static_assert(STAGE % 4096 == 0, "whole 1 KB loads per wave");
+  using C = Q4Cfg<ABITS, BBITS, GM>;
+  constexpr bool GROUPED = GM != Q4_CHANNEL;
+  constexpr int RBA = C::RBA, RBB = C::RBB, SA = C::SA, LPW = C::LPW, NS = C::NS;
+  constexpr int LPS = LPW + C::kScaleRows;                            // direct loads per wave per stage
   constexpr int TI = QWM / 32, TJ = QWN / 32;
   extern __shared__ __attribute__((aligned(1024))) uint8_t q4_smem[];
   __shared__ __attribute__((aligned(16))) float s_rs[QBM];
@@ -119,62 +157,67 @@ gemm_q4_pipe_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B
   xcd_tile(blockIdx.x, gridDim.x, n_tiles_n, gm, &tm, &tn);
   const int64_t m0 = (int64_t)tm * QBM;
   const int32_t n0 = tn * QBN;
-  const int nk = K / QBK;
+  const int nkf = K / QBK, nk = (K + QBK - 1) / QBK;                  // whole stages, stages (the last may be half a one)
   const int64_t KA = (int64_t)K * ABITS / 8, KB = (int64_t)K * BBITS / 8;   // row bytes in memory
 
-  // byte o of a stage: A tile rows first, then B tile rows; lane p of load j
-  // of wave w covers bytes 1024*(w*LPW + j) + 16p
   // Per-lane source offsets of this wave's direct loads from the tile's first
   // row (fixed over the contraction; a stage advances the base by a row's
   // stage bytes): byte o of a stage holds A tile rows first, then B tile
   // rows; lane p of load j of wave w covers bytes 1024*(w*LPW + j) + 16p.
+  // In a half stage (K a multiple of 64 only) the lanes of a row's upper half
+  // re-read the lower one.
   const uint8_t* a_tile = A + m0 * KA;
   const uint8_t* b_tile = B + (int64_t)n0 * KB;
   uint32_t voff[LPW];
 #pragma unroll
   for (int j = 0; j < LPW; ++j) {
     const int blk = w * LPW + j;                                     // wave-uniform
-    const int o = blk * 1024 + 16 * lane;
-    if (blk * 1024 < SA) {
-      const int row = o / RBA, phys = (o % RBA) / 16;
-      const int chunk = RBA == 64 ? (phys ^ ((row >> 2) & 3)) : (phys ^ ((row >> 3) & 1));
+    const bool is_a = blk * 1024 < SA;
+    const int o = blk * 1024 + 16 * lane - (is_a ? 0 : SA);
+    if (is_a) {
+      const int row = o / RBA, chunk = q4_swz<RBA>(row, (o % RBA) / 16);
       voff[j] = (uint32_t)(min((int64_t)row, M - 1 - m0) * KA + 16 * chunk);
     } else {
-      const int ob = o - SA;
-      const int row = ob / RBB, phys = (ob % RBB) / 16;
-      const int chunk = RBB == 64 ? (phys ^ ((row >> 2) & 3)) : (phys ^ ((row >> 3) & 1));
+      const int row = o / RBB, chunk = q4_swz<RBB>(row, (o % RBB) / 16);
       voff[j] = (uint32_t)(min((int64_t)row, (int64_t)N - 1 - n0) * KB + 16 * chunk);
     }
   }
+  const int gsteps = GROUPED ? group / 64 : 1;                       // half stages per group
+  const int ncl = min(n0 + wn * QWN + lane, N - 1);                  // the column whose scales this lane loads
   auto issue = [&](int st) {
-    uint8_t* base = q4_smem + (st % QNS) * STAGE;
+    uint8_t* base = q4_smem + (st % NS) * C::kStage;
 #pragma unroll
     for (int j = 0; j < LPW; ++j) {
       const int blk = w * LPW + j;
-      const uint8_t* src = blk * 1024 < SA ? a_tile + (int64_t)st * RBA + voff[j] : b_tile + (int64_t)st * RBB + voff[j];
+      const bool is_a = blk * 1024 < SA;
+      const int rb = is_a ? RBA : RBB;
+      uint32_t off = voff[j];
+      if (st >= nkf) {
+        const int o = blk * 1024 + 16 * lane - (is_a ? 0 : SA);
+        const int chunk = is_a ? q4_swz<RBA>(o / RBA, (o % RBA) / 16) : q4_swz<RBB>(o / RBB, (o % RBB) / 16);
+        if (16 * chunk >= rb / 2) off -= rb / 2;
+      }
+      const uint8_t* src = (is_a ? a_tile : b_tile) + (int64_t)st * rb + off;
       __builtin_amdgcn_global_load_lds((q4_glb_void_t*)src, (q4_lds_void_t*)(base + blk * 1024), 16, 0, 0);
+    }
+#pragma unroll
+    for (int h = 0; h < C::kScaleRows; ++h) {
+      const int g = min(GM == Q4_G128 ? st : (2 * st + h) / gsteps, K / group - 1);
+      __builtin_amdgcn_global_load_lds((q4_glb_void_t*)(cs + (int64_t)g * sstride + ncl),
+                                       (q4_lds_void_t*)(base + SA + C::SB + (4 * h + w) * 256), 4, 0, 0);
     }
   };
 
-  // row scales and this lane's column scales first (their waits leave the
-  // stage loads in flight)
-  for (int i = tid; i < QBM; i += 256) s_rs[i] = rs[min(m0 + i, M - 1)];
-  int32_t ncol[TJ];
+  // row scales and per-channel column scales first, into registers (their
+  // waits leave the stage loads in flight)
+  const float rsv = tid < QBM ? rs[min(m0 + tid, M - 1)] : 0.f;
   float csn[TJ];
 #pragma unroll
-  for (int j = 0; j < TJ; ++j) {
-    ncol[j] = n0 + wn * QWN + 32 * j + l32;
-    csn[j] = GROUPED ? 0.f : cs[min(ncol[j], N - 1)];
-  }
-  const int gsteps = GROUPED ? group / QBK : 0;
-  float gsc[TJ];               // scales of the group being accumulated
-  if constexpr (GROUPED) {
+  for (int j = 0; j < TJ; ++j) csn[j] = GROUPED ? 0.f : cs[min(n0 + wn * QWN + 32 * j + l32, N - 1)];
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) gsc[j] = cs[min(ncol[j], N - 1)];
-  }
-#pragma unroll
-  for (int st = 0; st < QNS - 1; ++st)
+  for (int st = 0; st < NS - 1; ++st)
     if (st < nk) issue(st);
+  if (tid < QBM) s_rs[tid] = rsv;
 
   i32x16 acc[TI][TJ];
   f32x16 S[GROUPED ? TI : 1][GROUPED ? TJ : 1];
@@ -189,17 +232,35 @@ gemm_q4_pipe_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B
       for (int j = 0; j < TJ; ++j) S[i][j] = f32x16{};
   }
 
-  // Fragments by contraction half kk (32 elements): half 1 of a stage is read
-  // while half 0's products run, half 0 of the next stage while half 1's run;
-  // one MFMA goes out before each read so that the reads run under them.
+  Q4Raw<ABITS> ra[TI];
+  Q4Raw<BBITS> rb[TJ];
+  auto read_half = [&](int kt, int h) {
+    const uint8_t* sa = q4_smem + (kt % NS) * C::kStage;
+#pragma unroll
+    for (int i = 0; i < TI; ++i) ra[i] = q4_read<ABITS>(sa, wm * QWM + 32 * i + l32, h, hl);
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) rb[j] = q4_read<BBITS>(sa + SA, wn * QWN + 32 * j + l32, h, hl);
+  };
+  // the scales of half h's group for this lane's columns, times 2^-SH:
+  // (float)acc * (s_g 2^-SH) is the same real number as (float)(acc >> SH) * s_g
+  // (acc is an exact multiple of 2^SH below 2^24, and scaling s_g by a power of
+  // two is exact), so it rounds the same; the shift is saved on every element
+  float gss[TJ];
+  auto read_scales = [&](int kt, int h) {
+    const float* src = reinterpret_cast<const float*>(q4_smem + (kt % NS) * C::kStage + SA + C::SB + (4 * h + w) * 256);
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) gss[j] = mul_rn(src[32 * j + l32], 1.f / (float)(1 << SH));
+  };
+  auto fold = [&](int i, int j) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) S[i][j][v] = add_rn(S[i][j][v], mul_rn((float)acc[i][j][v], gss[j]));
+  };
   i32x4 af[2][TI], bf[2][TJ];
-  auto read_half = [&](int kt, int kk) {
-    const uint8_t* sa = q4_smem + (kt % QNS) * STAGE;
-    const uint8_t* sb = sa + SA;
+  auto widen = [&](int kk) {
 #pragma unroll
-    for (int i = 0; i < TI; ++i) af[kk][i] = q4_frag<ABITS, BBITS>(sa, wm * QWM + 32 * i + l32, kk, hl);
+    for (int i = 0; i < TI; ++i) af[kk][i] = q4_step<ABITS, BBITS>(ra[i], kk);
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) bf[kk][j] = q4_frag<BBITS, ABITS>(sb, wn * QWN + 32 * j + l32, kk, hl);
+    for (int j = 0; j < TJ; ++j) bf[kk][j] = q4_step<BBITS, ABITS>(rb[j], kk);
   };
   auto products = [&](int kk) {
 #pragma unroll
@@ -208,60 +269,66 @@ gemm_q4_pipe_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B
       for (int j = 0; j < TJ; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[kk][i], bf[kk][j], acc[i][j], 0, 0, 0);
   };
-  auto interleave = [&]() {
+  // First products of a group: each tile's sums of the group before are folded
+  // (zeros before the first group), then its accumulators start anew.
+  auto restart = [&]() {
 #pragma unroll
-    for (int r = 0; r < TI + TJ; ++r) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
-    }
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) {
+        fold(i, j);
+        acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[0][i], bf[0][j], i32x16{}, 0, 0, 0);
+      }
   };
-  static_assert(TI * TJ == TI + TJ, "as many products as reads per half");
 
   // Waiting for stage s (its loads landed; every wave has finished reading
-  // stage s - 1) frees slot (s - 1) % QNS for stage s + QNS - 1.
-  q4_wait_stage<LPW, QNS - 2>(nk - 1);
-  if (QNS - 1 < nk) issue(QNS - 1);
+  // stage s - 1) frees slot (s - 1) % NS for stage s + NS - 1.  The next half
+  // is read while this one's products run, both steps of it where kEarly: the
+  // registers hold that but for two int8 operands, and beside the fold at any
+  // half (after the last half: an unused read of a stage slot).
+  constexpr bool kEarly = GM != Q4_GROUP && !(ABITS == 8 && BBITS == 8);
+  q4_wait_stage<LPS, NS - 2>(nk - 1);
+  if (NS - 1 < nk) issue(NS - 1);
   read_half(0, 0);
-  for (int kt = 0; kt < nk; ++kt) {
-    __builtin_amdgcn_sched_barrier(0);
-    products(0);
-    read_half(kt, 1);
-    interleave();
-    __builtin_amdgcn_sched_barrier(0);
-    // (on the last stage: a full wait and barrier, nothing left to issue)
-    q4_wait_stage<LPW, QNS - 2>(nk - 2 - kt);
-    if (kt + QNS < nk) issue(kt + QNS);
-    __builtin_amdgcn_sched_barrier(0);
-    // after the last stage this reads a stage slot whose values go unused
-    products(1);
-    read_half(kt + 1, 0);
-    interleave();
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (GROUPED) {
-      if ((kt + 1) % gsteps == 0) {
-        // group g = (kt + 1) / gsteps - 1 ends here: fold it, fetch the next group's scales
-        const int gn = (kt + 1) / gsteps;
-        // (float)acc * (s_g 2^-SH) is the same real number as
-        // (float)(acc >> SH) * s_g (acc is an exact multiple of 2^SH below
-        // 2^24, and scaling s_g by a power of two is exact), so it rounds the
-        // same; the shift is saved on every element
-        float gss[TJ];
+  if constexpr (GROUPED) {
 #pragma unroll
-        for (int j = 0; j < TJ; ++j) gss[j] = mul_rn(gsc[j], 1.f / (float)(1 << SH));
-#pragma unroll
-        for (int i = 0; i < TI; ++i)
-#pragma unroll
-          for (int j = 0; j < TJ; ++j) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) S[i][j][v] = add_rn(S[i][j][v], mul_rn((float)acc[i][j][v], gss[j]));
-            acc[i][j] = i32x16{};
-          }
-        if (gn * gsteps < nk) {
-#pragma unroll
-          for (int j = 0; j < TJ; ++j) gsc[j] = cs[(int64_t)gn * sstride + min(ncol[j], N - 1)];
-        }
-      }
+    for (int j = 0; j < TJ; ++j) gss[j] = 0.f;
+  }
+  // next(): whatever comes before the next half's reads, and those
+  auto half = [&](int kt, int h, bool start, auto&& next) {
+    widen(0);
+    if constexpr (kEarly) {
+      widen(1);
+      next();
     }
+    if (GROUPED && start) restart();
+    else products(0);
+    if (GROUPED && (GM == Q4_GROUP || h == 0)) read_scales(kt, GM == Q4_GROUP ? h : 0);
+    if constexpr (!kEarly) {
+      widen(1);
+      products(1);
+      next();
+    } else {
+      products(1);
+    }
+  };
+  for (int kt = 0; kt < nkf; ++kt) {
+    half(kt, 0, GM == Q4_G128 || (GM == Q4_GROUP && (2 * kt) % gsteps == 0), [&]() { read_half(kt, 1); });
+    half(kt, 1, GM == Q4_GROUP && (2 * kt + 1) % gsteps == 0, [&]() {
+      __builtin_amdgcn_sched_barrier(0);
+      // (on the last stage: a full wait and barrier, nothing left to issue)
+      q4_wait_stage<LPS, NS - 2>(nk - 2 - kt);
+      if (kt + NS < nk) issue(kt + NS);
+      __builtin_amdgcn_sched_barrier(0);
+      read_half(kt + 1, 0);
+    });
+  }
+  if (nkf < nk) half(nkf, 0, GM == Q4_G128 || (GM == Q4_GROUP && (2 * nkf) % gsteps == 0), []() {});
+  if constexpr (GROUPED) {
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) fold(i, j);
   }
 
   // Epilogue: the dequantized fp16 tile of each wave is staged in LDS and
@@ -297,26 +364,30 @@ gemm_q4_pipe_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B
   }
 }
 
-template <int ABITS, int BBITS, bool GROUPED>
+template <int ABITS, int BBITS, int GM>
 static hipError_t launch_q4(const GemmArgs& g, const Q4Segs& sg, int32_t group, int32_t sstride, hipStream_t s) {
-  constexpr int STAGE = QBM * QBK * ABITS / 8 + QBN * QBK * BBITS / 8;
-  constexpr size_t lds = (size_t)QNS * STAGE > (size_t)4 * QWM * (QWN + 8) * 2 ? (size_t)QNS * STAGE
-                                                                             : (size_t)4 * QWM * (QWN + 8) * 2;
-  auto kern = gemm_q4_pipe_kernel<ABITS, BBITS, GROUPED>;
-  hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  using C = Q4Cfg<ABITS, BBITS, GM>;
+  auto kern = gemm_q4_pipe_kernel<ABITS, BBITS, GM>;
+  hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::kLds);
   if (e != hipSuccess) return e;
   const int tn = (g.N + QBN - 1) / QBN;
   const int64_t tm = (g.M + QBM - 1) / QBM;
   KernelScope ks("gemm_q4_pipe", s);
-  QSVD_LAUNCH(ks, kern, dim3((unsigned)(tm * tn)), dim3(256), lds, s, (const uint8_t*)g.a, (const uint8_t*)g.b,
+  QSVD_LAUNCH(ks, kern, dim3((unsigned)(tm * tn)), dim3(256), C::kLds, s, (const uint8_t*)g.a, (const uint8_t*)g.b,
               g.row_scale, g.col_scale, sstride, g.M, g.N, g.K, group, tn, xcd_group_rows(tm, tn), sg);
   return hipGetLastError();
+}
+
+template <int ABITS, int BBITS>
+static hipError_t launch_q4_grouped(const GemmArgs& g, const Q4Segs& sg, int32_t group, int32_t sstride, hipStream_t s) {
+  return group == QBK ? launch_q4<ABITS, BBITS, Q4_G128>(g, sg, group, sstride, s)
+                      : launch_q4<ABITS, BBITS, Q4_GROUP>(g, sg, group, sstride, s);
 }
 
 hipError_t launch_gemm_q4(const GemmArgs& g, int32_t abits, int32_t wbits, int32_t group, int32_t sstride,
                           hipStream_t s) {
   if (g.M == 0 || g.N == 0) return hipSuccess;
-  if (g.K % QBK || (group && (group % QBK || g.K % group))) return hipErrorInvalidValue;
+  if (g.K % 64 || (group && (group % 64 || g.K % group))) return hipErrorInvalidValue;
   if ((abits != 8 && abits != 4) || (wbits != 8 && wbits != 4) || (wbits == 4 && !group)) return hipErrorInvalidValue;
   for (int i = 0; i < g.n_seg; ++i)
     if (g.seg[i].n0 % 8 || g.seg[i].n % 8 || g.seg[i].ld % 8 || ((uintptr_t)g.seg[i].ptr & 15))
@@ -334,11 +405,11 @@ hipError_t launch_gemm_q4(const GemmArgs& g, int32_t abits, int32_t wbits, int32
     }
   }
   hipError_t e;
-  if (abits == 8 && wbits == 4) e = launch_q4<8, 4, true>(g, sg, group, sstride, s);
-  else if (abits == 4 && wbits == 4) e = launch_q4<4, 4, true>(g, sg, group, sstride, s);
-  else if (abits == 4 && group) e = launch_q4<4, 8, true>(g, sg, group, sstride, s);
-  else if (abits == 4) e = launch_q4<4, 8, false>(g, sg, 0, sstride, s);
-  else e = launch_q4<8, 8, true>(g, sg, group, sstride, s);     // 8-bit codes, per-group scales
+  if (abits == 8 && wbits == 4) e = launch_q4_grouped<8, 4>(g, sg, group, sstride, s);
+  else if (abits == 4 && wbits == 4) e = launch_q4_grouped<4, 4>(g, sg, group, sstride, s);
+  else if (abits == 4 && group) e = launch_q4_grouped<4, 8>(g, sg, group, sstride, s);
+  else if (abits == 4) e = launch_q4<4, 8, Q4_CHANNEL>(g, sg, 0, sstride, s);
+  else e = launch_q4_grouped<8, 8>(g, sg, group, sstride, s);     // 8-bit codes, per-group scales
   if (e != hipSuccess || !g.cq) return e;
   return launch_quantize_rows(g.seg[0].ptr, g.M, g.N, g.seg[0].ld, g.abits, 1.f, g.cq, g.sc, s, "latent_quant");
 }

@@ -352,6 +352,30 @@ def test_prefill_bitexact_qwen2vl_w4a8(qwen):
     _check_mixed(ol, H.Prefill(dl, 640, debug=False).run(H.dev(X)).result(), X, 8)
 
 
+@pytest.mark.parametrize("d,r,w_bits,w_group,abits,M", [
+    (64, 64, 8, 0, 8, 33),          # contractions of one half stage (64 of 128 elements)
+    (192, 320, 8, 0, 8, 130),       # whole stages and a half one, a ragged row tile
+    (192, 192, 8, 0, 8, 1400),      # the same on the 256 x 256 tiles
+    (192, 320, 4, 64, 8, 130),      # int4: groups of half a stage, a half stage at the end
+    (192, 320, 4, 64, 4, 33),
+    (384, 384, 4, 192, 8, 130),     # groups of three halves
+    (384, 768, 4, 384, 4, 130),     # groups of three stages
+    (256, 128, 4, 128, 4, 257),     # a group per stage
+    (256, 384, 8, 128, 8, 130),     # int8 weights with groups
+    (320, 192, 8, 64, 4, 130),
+    (192, 320, 8, 0, 4, 130),       # int4 activations, one scale per channel
+])
+def test_projection_bitexact_stage_edges(d, r, w_bits, w_group, abits, M):
+    """The tiled projections where their contraction stages, scale groups and
+    tiles have their edges: every output bit-exact."""
+    wide = M > 1000
+    L = configs.LayerShape(d=d, n_q_heads=32 if wide else 6, n_kv_heads=32 if wide else 2, head_dim=128 if wide else 64, r=r)
+    ol, dl = _random_factor_layer(L, d + r + M, w_bits, w_group)
+    X = gen.random_rows(d + M, (M, d), 1.0)
+    H.say(f"projection edges d={d} r={r} w{w_bits} g{w_group} a{abits} M={M}")
+    _check_mixed(ol, H.Prefill(dl, M, debug=False, abits=abits).run(H.dev(X)).result(), X, abits)
+
+
 def test_prefill_masks_leave_other_outputs(tiny):
     wl, ol, dl = tiny
     X = gen.fill_activations(wl, 40)

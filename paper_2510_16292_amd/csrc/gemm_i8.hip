@@ -180,14 +180,14 @@ gemm_i8_pipe_kernel(const int8_t* __restrict__ A, const int8_t* __restrict__ B,
 
   // Scales first, into a register: their wait then leaves the stage loads in
   // flight (fp16 operands: a NULL scale vector means no scale).
-  static_assert(BM + BN == C::kThreads, "one scale per thread");
+  static_assert(BM + BN <= C::kThreads, "at most one scale per thread");
   const float* sp = tid < BM ? rs : cs;
   const int64_t si = tid < BM ? min(m0 + tid, M - 1) : (int64_t)min(n0 + tid - BM, N - 1);
   const float sv = (!F16 || sp) ? sp[si] : 1.f;
 #pragma unroll
   for (int st = 0; st < NS - 1; ++st)
     if (st < nk) issue(st);
-  (tid < BM ? s_rs[tid] : s_cs[tid - BM]) = sv;
+  if (tid < BM + BN) (tid < BM ? s_rs[tid] : s_cs[tid - BM]) = sv;
 
   Acc acc[TI][TJ];
 #pragma unroll
@@ -224,7 +224,7 @@ gemm_i8_pipe_kernel(const int8_t* __restrict__ A, const int8_t* __restrict__ B,
   // run under the products and every wait the compiler places before a
   // product only covers reads issued before it.
   auto interleave = [&]() {
-    if constexpr (C::kWaves == 8) return;     // (its reads go out before all of its products)
+    if constexpr (C::kWaves == 8 || TI * TJ < TI + TJ) return;   // (the reads go out before all of the products)
 #pragma unroll
     for (int r = 0; r < TI + TJ; ++r) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
@@ -232,7 +232,6 @@ gemm_i8_pipe_kernel(const int8_t* __restrict__ A, const int8_t* __restrict__ B,
     }
     __builtin_amdgcn_sched_group_barrier(0x008, TI * TJ - (TI + TJ), 0);
   };
-  static_assert(TI * TJ >= TI + TJ, "at least as many products as reads per step");
 
   // Waiting for stage s (its loads landed; every wave has finished reading
   // stage s - 1) frees slot (s - 1) % NS for stage s + NS - 1.
@@ -252,7 +251,7 @@ gemm_i8_pipe_kernel(const int8_t* __restrict__ A, const int8_t* __restrict__ B,
       // after the last stage's last step: an unused read of a stage slot,
       // which keeps this loop free of branches around products
       read_step(kk == PKK - 1 ? kt + 1 : kt, (kk + 1) % PKK);
-      if (C::kWaves == 8) __builtin_amdgcn_sched_barrier(0);
+      if (C::kWaves == 8 || TI * TJ < TI + TJ) __builtin_amdgcn_sched_barrier(0);
       products(kk);
       interleave();
     }
@@ -412,6 +411,12 @@ static DevSegs to_dev(const GemmArgs& g) {
 // Tiles one XCD runs at once: its 32 CUs, one workgroup each.
 constexpr int kGemmTilesPerXcd = 32;
 
+// Fewer 128 x 128 tiles than this: 64 x 64 instead (whole W8A8 projections of
+// d = 4096, r = 1536, N = 12288, whose down-projection has 12 tiles per 128
+// tokens: 33 tokens 45.8 -> 34.2 us, 260 tokens 58.2 -> 49.9, 900 tokens 74.4
+// -> 67.3).
+constexpr int64_t kSmallTiles = 128;
+
 template <int BM, int BN, int WM, int WN, int NS, bool DBG, bool F16 = false, int RS = 0>
 static hipError_t launch_pipe(const GemmArgs& g, const DevSegs& sg, hipStream_t s, const RopeEpi& re = RopeEpi{}) {
   using C = PipeCfg<BM, BN, WM, WN, NS>;
@@ -435,12 +440,14 @@ hipError_t launch_gemm_i8(const GemmArgs& g, hipStream_t s) {
     if (g.seg[i].n0 % 8 || g.seg[i].n % 8 || g.seg[i].ld % 8 || ((uintptr_t)g.seg[i].ptr & 15))
       return hipErrorInvalidValue;
   const DevSegs sg = to_dev(g);
-  // 256 x 256 tiles once they fill the chip, 128 x 128 otherwise (and for
-  // the accumulator dumps)
+  // 256 x 256 tiles once they fill the chip, 64 x 64 where even 128 x 128 ones
+  // leave most of it idle, 128 x 128 otherwise (and for the accumulator dumps)
   const int64_t big_tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
+  const int64_t tiles = ((g.M + 127) / 128) * ((g.N + 127) / 128);
   hipError_t e = g.dbg ? launch_pipe<128, 128, 64, 64, 4, true>(g, sg, s)
                  : big_tiles >= 256 ? launch_pipe<256, 256, 128, 64, 2, false>(g, sg, s)
-                                    : launch_pipe<128, 128, 64, 64, 4, false>(g, sg, s);
+                 : tiles < kSmallTiles ? launch_pipe<64, 64, 32, 32, 4, false>(g, sg, s)
+                                       : launch_pipe<128, 128, 64, 64, 4, false>(g, sg, s);
   if (e != hipSuccess || !g.cq) return e;
   return launch_quantize_rows(g.seg[0].ptr, g.M, g.N, g.seg[0].ld, g.abits, 1.f, g.cq, g.sc, s, "latent_quant");
 }

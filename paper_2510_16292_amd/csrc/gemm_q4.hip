@@ -33,7 +33,7 @@ namespace qsvd {
 typedef __attribute__((address_space(3))) void q4_lds_void_t;
 typedef __attribute__((address_space(1))) void q4_glb_void_t;
 
-constexpr int QBM = 128, QBN = 128, QWM = 64, QWN = 64, QBK = 128;
+constexpr int QBK = 128;
 
 template <int N>
 __device__ __forceinline__ void q4_wait_barrier() {
@@ -121,26 +121,28 @@ __device__ __forceinline__ _Float16* q4_col(const Q4Segs& sg, int32_t n, int64_t
 // any other multiple of 64.
 enum { Q4_CHANNEL = 0, Q4_G128 = 1, Q4_GROUP = 2 };
 
-template <int ABITS, int BBITS, int GM>
+template <int ABITS, int BBITS, int GM, int QT>
 struct Q4Cfg {
+  static constexpr int QBM = QT, QBN = QT, QWM = QT / 2, QWN = QT / 2;   // tile, and its four waves'
   static constexpr int RBA = QBK * ABITS / 8, RBB = QBK * BBITS / 8;   // stage row bytes
   static constexpr int SA = QBM * RBA, SB = QBN * RBB;
   static constexpr int kScaleRows = GM;                                // scale rows per stage: 0, 1 or 2
-  static constexpr int kStage = SA + SB + kScaleRows * QBN * 2 * 4;    // each of the four waves has its 64 columns' scales
+  static constexpr int kStage = SA + SB + kScaleRows * 1024;           // each of the four waves has 64 columns' scales
   static constexpr int LPW = (SA + SB) / 4096;                         // 16-byte direct loads per wave per stage
   static constexpr int NS = SA + SB <= 16384 ? 4 : SA + SB <= 24576 ? 3 : 2;
   static constexpr int kOut = 4 * QWM * (QWN + 8) * 2;
   static constexpr size_t kLds = NS * kStage > kOut ? NS * kStage : kOut;
   static_assert(2 * (kLds + 1024) <= 160 * 1024, "two workgroups per CU");
-  static_assert(LPW % 2 == 0 && SA % 2048 == 0, "block parity of load j is j's");
+  static_assert((SA + SB) % 4096 == 0 && SA % 1024 == 0, "whole 1 KB loads per wave");
 };
 
-template <int ABITS, int BBITS, int GM>
+template <int ABITS, int BBITS, int GM, int QT>
 __global__ void __launch_bounds__(256, 2)
 gemm_q4_pipe_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B,
                     const float* __restrict__ rs, const float* __restrict__ cs, int32_t sstride,
                     int64_t M, int32_t N, int32_t K, int32_t group, int32_t n_tiles_n, int32_t gm, Q4Segs sg) {
-  using C = Q4Cfg<ABITS, BBITS, GM>;
+  using C = Q4Cfg<ABITS, BBITS, GM, QT>;
+  constexpr int QBM = C::QBM, QBN = C::QBN, QWM = C::QWM, QWN = C::QWN;
   constexpr bool GROUPED = GM != Q4_CHANNEL;
   constexpr int RBA = C::RBA, RBB = C::RBB, SA = C::SA, LPW = C::LPW, NS = C::NS;
   constexpr int LPS = LPW + C::kScaleRows;                            // direct loads per wave per stage
@@ -364,18 +366,32 @@ gemm_q4_pipe_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B
   }
 }
 
-template <int ABITS, int BBITS, int GM>
-static hipError_t launch_q4(const GemmArgs& g, const Q4Segs& sg, int32_t group, int32_t sstride, hipStream_t s) {
-  using C = Q4Cfg<ABITS, BBITS, GM>;
-  auto kern = gemm_q4_pipe_kernel<ABITS, BBITS, GM>;
+// 128 x 128 tiles from so many on, else 64 x 64 (four waves of one 32 x 32
+// product each): these widen twice the operand elements per output, but four
+// times as many workgroups take part.  W4A8, tiles of 128, us with 128 and 64:
+// 32 tiles 34.8, 17.4; 88 tiles 36.7, 23.5; 112 tiles 17.9, 11.1; 396 tiles
+// 23.9, 29.1; 504 tiles 24.3, 36.3.
+constexpr int64_t kQ4BigTiles = 256;
+
+template <int ABITS, int BBITS, int GM, int QT>
+static hipError_t launch_q4_tiles(const GemmArgs& g, const Q4Segs& sg, int32_t group, int32_t sstride, hipStream_t s) {
+  using C = Q4Cfg<ABITS, BBITS, GM, QT>;
+  auto kern = gemm_q4_pipe_kernel<ABITS, BBITS, GM, QT>;
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::kLds);
   if (e != hipSuccess) return e;
-  const int tn = (g.N + QBN - 1) / QBN;
-  const int64_t tm = (g.M + QBM - 1) / QBM;
+  const int tn = (g.N + QT - 1) / QT;
+  const int64_t tm = (g.M + QT - 1) / QT;
   KernelScope ks("gemm_q4_pipe", s);
   QSVD_LAUNCH(ks, kern, dim3((unsigned)(tm * tn)), dim3(256), C::kLds, s, (const uint8_t*)g.a, (const uint8_t*)g.b,
               g.row_scale, g.col_scale, sstride, g.M, g.N, g.K, group, tn, xcd_group_rows(tm, tn), sg);
   return hipGetLastError();
+}
+
+template <int ABITS, int BBITS, int GM>
+static hipError_t launch_q4(const GemmArgs& g, const Q4Segs& sg, int32_t group, int32_t sstride, hipStream_t s) {
+  const int64_t tiles = ((g.M + 127) / 128) * ((g.N + 127) / 128);
+  return tiles >= kQ4BigTiles ? launch_q4_tiles<ABITS, BBITS, GM, 128>(g, sg, group, sstride, s)
+                              : launch_q4_tiles<ABITS, BBITS, GM, 64>(g, sg, group, sstride, s);
 }
 
 template <int ABITS, int BBITS>

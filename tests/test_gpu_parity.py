@@ -364,6 +364,10 @@ def test_prefill_bitexact_qwen2vl_w4a8(qwen):
     (256, 384, 8, 128, 8, 130),     # int8 weights with groups
     (320, 192, 8, 64, 4, 130),
     (192, 320, 8, 0, 4, 130),       # int4 activations, one scale per channel
+    (192, 320, 4, 64, 8, 1400),     # and on the 128 x 128 tiles of the 4-bit products
+    (256, 128, 4, 128, 8, 1400),
+    (192, 192, 8, 64, 8, 1400),
+    (256, 128, 8, 0, 4, 1400),
 ])
 def test_projection_bitexact_stage_edges(d, r, w_bits, w_group, abits, M):
     """The tiled projections where their contraction stages, scale groups and

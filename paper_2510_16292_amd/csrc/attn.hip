@@ -1021,35 +1021,43 @@ latent_attn_h16_kernel(const _Float16* __restrict__ qt, const uint8_t* __restric
 // order the attention kernels write.  With m = max m_c and
 // w_c = 2^(m_c - m) l_c / sum, the result O[vb][h][x] = sum_c w_c (O_c / l_c)[h][x]
 // is written head-major [vb][hp][r] at heads hb*HB ...
-// A workgroup takes 2048 consecutive partial elements (2048 / (4 HB) latent
-// quads x HB heads x 4); its threads first compute all the per-(chunk, head)
-// weights into LDS (256 / HB lanes per head, chunks strided over them), then
-// each thread streams 8 elements (two heads x 4 columns) of every chunk.
+// A workgroup takes 2048 / CG consecutive partial elements (2048 / CG / (4 HB)
+// latent quads x HB heads x 4); its threads first compute all the per-(chunk,
+// head) weights into LDS (256 / HB lanes per head, chunks strided over them),
+// then each of its CG thread groups streams 8 elements (two heads x 4 columns)
+// per thread of every CG-th chunk, and the groups' sums are added through LDS
+// in a fixed order.  CG 1 reads the partials with the widest runs; with few
+// rows (24 workgroups for one sequence of r = 1536) the chip idles while each
+// walks all the chunks, and CG 8 makes eight times as many.
 // ---------------------------------------------------------------------------
 constexpr int kMergeElems = 2048;
 constexpr int kMergeBatch = 16;   // chunk partials in flight per thread (one round trip for <= 16 chunks)
 
-template <int HB>
+template <int HB, int CG>
 __global__ void __launch_bounds__(256)
 merge_latent_kernel(const _Float16* __restrict__ o_part, const float* __restrict__ ml_part,
                     const int32_t* __restrict__ seq_len, int32_t capacity, int32_t chunk, int32_t n_chunks,
                     int32_t n_launched, int32_t q_len, int32_t r, int32_t hp, _Float16* __restrict__ o_lat) {
   constexpr int LPH = 256 / HB;      // lanes per head in the weights phase
+  constexpr int ELEMS = kMergeElems / CG, TPG = 256 / CG;   // elements per workgroup, threads per group
   __shared__ float wgt[kMaxChunks * HB];
   const int n_hb = hp / HB;
   const int row = blockIdx.y, vb = row / n_hb, hb = row - vb * n_hb, tid = threadIdx.x;
+  const int cg = tid / TPG, gt = tid % TPG;
   const int L = min(seq_len[vb / q_len], capacity) - (q_len - 1 - vb % q_len);
   const int nv = L > 0 ? min(min((L + chunk - 1) / chunk, n_launched), kMaxChunks) : 0;
   const int64_t pb = (int64_t)row * n_chunks;
   // element e8 (8 halves): latent quad x4 = e8 / (HB / 2), heads 2*(e8 % (HB / 2)) and +1;
   // the first batch of partial loads goes out before the weights are known
-  const int64_t e0 = (int64_t)blockIdx.x * kMergeElems + 8 * tid;
+  const int64_t e0 = (int64_t)blockIdx.x * ELEMS + 8 * gt;
   const bool eok = e0 < (int64_t)r * HB;
   const _Float16* src = o_part + pb * (int64_t)r * HB + (eok ? e0 : 0);
   f16x8 v[kMergeBatch];
 #pragma unroll
-  for (int k = 0; k < kMergeBatch; ++k)
-    v[k] = (eok && k < nv) ? *reinterpret_cast<const f16x8*>(src + (int64_t)k * r * HB) : f16x8{};
+  for (int k = 0; k < kMergeBatch; ++k) {
+    const int c = cg + CG * k;
+    v[k] = (eok && c < nv) ? *reinterpret_cast<const f16x8*>(src + (int64_t)c * r * HB) : f16x8{};
+  }
   {
     const int h = tid / LPH, sub = tid % LPH;
     float m = -INFINITY;
@@ -1072,16 +1080,19 @@ merge_latent_kernel(const _Float16* __restrict__ o_part, const float* __restrict
   float acc[8];
 #pragma unroll
   for (int k = 0; k < 8; ++k) acc[k] = 0.f;
-  for (int c0 = 0; eok && c0 < nv; c0 += kMergeBatch) {
-    if (c0 > 0) {
+  for (int c0 = cg; eok && c0 < nv; c0 += CG * kMergeBatch) {
+    if (c0 > cg) {
 #pragma unroll
-      for (int k = 0; k < kMergeBatch; ++k)
-        v[k] = (c0 + k < nv) ? *reinterpret_cast<const f16x8*>(src + (int64_t)(c0 + k) * r * HB) : f16x8{};
+      for (int k = 0; k < kMergeBatch; ++k) {
+        const int c = c0 + CG * k;
+        v[k] = c < nv ? *reinterpret_cast<const f16x8*>(src + (int64_t)c * r * HB) : f16x8{};
+      }
     }
 #pragma unroll
     for (int k = 0; k < kMergeBatch; ++k) {
-      if (c0 + k >= nv) continue;
-      const float w0 = wgt[(c0 + k) * HB + h0], w1 = wgt[(c0 + k) * HB + h0 + 1];
+      const int c = c0 + CG * k;
+      if (c >= nv) continue;
+      const float w0 = wgt[c * HB + h0], w1 = wgt[c * HB + h0 + 1];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         acc[q] = fmaf(w0, (float)v[k][q], acc[q]);
@@ -1089,22 +1100,37 @@ merge_latent_kernel(const _Float16* __restrict__ o_part, const float* __restrict
       }
     }
   }
-  // The workgroup's kMergeElems / HB latent columns of its HB heads go
-  // through LDS, so that each head row leaves as 16-byte runs.
-  constexpr int COLS = kMergeElems / HB, OLD = COLS + 8;
+  if constexpr (CG > 1) {
+    __shared__ __attribute__((aligned(16))) f32x4 gsum[CG - 1][2][TPG];
+    if (cg > 0) {
+      gsum[cg - 1][0][gt] = f32x4{acc[0], acc[1], acc[2], acc[3]};
+      gsum[cg - 1][1][gt] = f32x4{acc[4], acc[5], acc[6], acc[7]};
+    }
+    __syncthreads();
+    if (cg == 0)
+#pragma unroll
+      for (int k = 0; k < CG - 1; ++k)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc[q] += gsum[k][q >> 2][gt][q & 3];
+  }
+  // The workgroup's ELEMS / HB latent columns of its HB heads go through LDS,
+  // so that each head row leaves as 16-byte runs.
+  constexpr int COLS = ELEMS / HB, OLD = COLS + 8;
   __shared__ __attribute__((aligned(16))) _Float16 ot[HB * OLD];
   const int xl = 4 * x4 - blockIdx.x * COLS;
+  if (cg == 0) {
 #pragma unroll
-  for (int hh = 0; hh < 2; ++hh) {
-    const f16x4 o4 = {(_Float16)acc[4 * hh], (_Float16)acc[4 * hh + 1], (_Float16)acc[4 * hh + 2],
-                      (_Float16)acc[4 * hh + 3]};
-    *reinterpret_cast<f16x4*>(ot + (h0 + hh) * OLD + xl) = o4;
+    for (int hh = 0; hh < 2; ++hh) {
+      const f16x4 o4 = {(_Float16)acc[4 * hh], (_Float16)acc[4 * hh + 1], (_Float16)acc[4 * hh + 2],
+                        (_Float16)acc[4 * hh + 3]};
+      *reinterpret_cast<f16x4*>(ot + (h0 + hh) * OLD + xl) = o4;
+    }
   }
   __syncthreads();
-  static_assert(HB * COLS / 8 == 256, "one 16-byte run per thread");
-  const int hr = tid / (COLS / 8), c8 = 8 * (tid % (COLS / 8));
+  static_assert(COLS % 8 == 0 && HB * COLS / 8 == TPG, "one 16-byte run per thread of a group");
+  const int hr = gt / (COLS / 8), c8 = 8 * (gt % (COLS / 8));
   const int col = blockIdx.x * COLS + c8;
-  if (col < r)
+  if (cg == 0 && col < r)
     *reinterpret_cast<f16x8*>(o_lat + ((int64_t)vb * hp + hb * HB + hr) * r + col) =
         *reinterpret_cast<const f16x8*>(ot + hr * OLD + c8);
 }
@@ -1299,7 +1325,9 @@ static AbsorbPlan plan_absorbed(const qsvd_layer& w, const qsvd_cache& c, int32_
   p.n0 = p.hb == kHeadBlk ? target_chunks((int)grows) : (int)(grows >= 256 ? 1 : 256 / grows);
   const int len = c.max_len > 0 ? c.max_len : 1;
   int ch = (len + p.n0 - 1) / p.n0;
-  const int gran = p.hb == kHeadBlk ? 16 : 64;      // 16-head plans: whole tiles and ring rounds
+  // whole tiles (16-head plans: and ring rounds): half a tile costs a whole
+  // one's time and a partial more to merge
+  const int gran = p.hb == kHeadBlk ? 32 : 64;
   ch = ((ch + gran - 1) / gran) * gran;
   p.chunk = ch;
   p.n_chunks = (len + ch - 1) / ch;
@@ -1431,6 +1459,30 @@ hipError_t launch_attn_absorbed(const AttnArgs& a, void* ws, hipStream_t s) {
   return absorbed_from_qt(a, p, b, s);
 }
 
+template <int HB, int CG>
+static hipError_t launch_merge_groups(const AttnArgs& a, const AbsorbPlan& p, int32_t rows, const _Float16* opart,
+                                      const float* ml, _Float16* olat, hipStream_t s) {
+  const qsvd_cache& c = *a.c;
+  KernelScope ks("merge_latent", s);
+  const dim3 grid((a.w->r * HB + kMergeElems / CG - 1) / (kMergeElems / CG), rows * p.n_hb);
+  QSVD_LAUNCH(ks, (merge_latent_kernel<HB, CG>), grid, dim3(256), 0, s, opart, ml, c.seq_len, c.capacity, p.chunk,
+              p.n0, p.n_chunks, a.q_len, a.w->r, p.hp, olat);
+  return hipGetLastError();
+}
+
+// Chunk groups per merge workgroup: eight (four) where one would leave a CU in
+// four (half the CUs) without a workgroup and the groups still have chunks to
+// share out.  One sequence of 1502 tokens, r = 1536: 22.8 us with one group
+// and 16-token chunks, 9.6 with eight and 32-token chunks.
+template <int HB>
+static hipError_t launch_merge(const AttnArgs& a, const AbsorbPlan& p, int32_t rows, const _Float16* opart,
+                               const float* ml, _Float16* olat, hipStream_t s) {
+  const int64_t wgs = (int64_t)((a.w->r * HB + kMergeElems - 1) / kMergeElems) * rows * p.n_hb;
+  if (wgs <= 64 && p.n_chunks >= 8) return launch_merge_groups<HB, 8>(a, p, rows, opart, ml, olat, s);
+  if (wgs <= 128 && p.n_chunks >= 8) return launch_merge_groups<HB, 4>(a, p, rows, opart, ml, olat, s);
+  return launch_merge_groups<HB, 1>(a, p, rows, opart, ml, olat, s);
+}
+
 // Merge the chunk partials into O_lat, then o = O_lat W^u_v.
 static hipError_t merge_and_project(const AttnArgs& a, const AbsorbPlan& p, const _Float16* opart, const float* ml,
                                     _Float16* olat, hipStream_t s) {
@@ -1438,16 +1490,9 @@ static hipError_t merge_and_project(const AttnArgs& a, const AbsorbPlan& p, cons
   const qsvd_cache& c = *a.c;
   const int32_t rows = c.batch * a.q_len;
   const int N = (w.n_q_heads + 2 * w.n_kv_heads) * w.head_dim;
-  {
-    KernelScope ks("merge_latent", s);
-    const dim3 grid((w.r * p.hb + kMergeElems - 1) / kMergeElems, rows * p.n_hb);
-    if (p.hb == 16)
-      QSVD_LAUNCH(ks, merge_latent_kernel<16>, grid, dim3(256), 0, s, opart, ml, c.seq_len, c.capacity, p.chunk,
-                  p.n0, p.n_chunks, a.q_len, w.r, p.hp, olat);
-    else
-      QSVD_LAUNCH(ks, merge_latent_kernel<kHeadBlk>, grid, dim3(256), 0, s, opart, ml, c.seq_len, c.capacity,
-                  p.chunk, p.n0, p.n_chunks, a.q_len, w.r, p.hp, olat);
-  }
+  hipError_t e = p.hb == 16 ? launch_merge<16>(a, p, rows, opart, ml, olat, s)
+                            : launch_merge<kHeadBlk>(a, p, rows, opart, ml, olat, s);
+  if (e != hipSuccess) return e;
   {
     KernelScope ks("vproj", s);
     QSVD_LAUNCH(ks, vproj_kernel, dim3(w.n_q_heads, w.head_dim / 16), dim3(64 * kVprojWaves), 0, s, olat,

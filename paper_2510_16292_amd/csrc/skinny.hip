@@ -23,9 +23,11 @@
 // m's codes and scale.  The first batch of weight loads is issued before this
 // so that its HBM latency overlaps the row pass.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "launch.h"
+
 #include "rowpass.h"
 
 namespace qsvd {
@@ -58,20 +60,20 @@ __device__ __forceinline__ void sk_store(const SkinnyOut& so, int64_t m, int32_t
   base[m * ld + (n - n0)] = to_f16(y);
 }
 
-// 16 int4 codes (8 bytes, element 2i in the low nibble of byte i) -> 16 int8.
-__device__ __forceinline__ i32x4 unpack16_i4(uint2 p) {
+// 16 int4 codes (8 bytes, element 2i in the low nibble of byte i) -> 16 int8
+// holding 16 * code, in order: each code's nibble moves to the high half of a
+// byte (three operations per eight codes, its sign bit on bit 7), two byte
+// permutes restore the order.  Ten operations, where exact codes take some
+// seventy; sums of products are exact multiples of 16 (per such operand) and
+// are shifted back before use.
+__device__ __forceinline__ i32x4 widen16_i4(uint2 p) {
   i32x4 o;
   const uint32_t w[2] = {p.x, p.y};
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    uint32_t lo = 0, hi = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      lo |= (uint32_t)((((int)(w[h] << (28 - 4 * e))) >> 28) & 0xff) << (8 * e);
-      hi |= (uint32_t)((((int)(w[h] << (12 - 4 * e))) >> 28) & 0xff) << (8 * e);
-    }
-    o[2 * h] = (int32_t)lo;
-    o[2 * h + 1] = (int32_t)hi;
+    const uint32_t even = (w[h] << 4) & 0xF0F0F0F0u, odd = w[h] & 0xF0F0F0F0u;
+    o[2 * h] = (int32_t)__builtin_amdgcn_perm(odd, even, 0x05010400u);
+    o[2 * h + 1] = (int32_t)__builtin_amdgcn_perm(odd, even, 0x07030602u);
   }
   return o;
 }
@@ -139,19 +141,19 @@ skinny_gemm_kernel(const void* __restrict__ a_src, int64_t lda, float clip, cons
     s_gscale[i] = i % kSkCols < cols && nn < N ? col_scale[(int64_t)(i / kSkCols) * sstride + nn] : 0.f;
   }
 
-  i32x4 bw[kSkBatch];
+  // weight codes as loaded: int4 ones are widened at their use, so that the
+  // row pass below runs while they arrive
+  using BRaw = std::conditional_t<WBITS == 8, i32x4, uint2>;
+  BRaw bw[kSkBatch];
   auto load_b = [&](int st0) {
 #pragma unroll
     for (int s = 0; s < kSkBatch; ++s) {
       const int st = st0 + s;
       const int32_t k = 64 * st + 16 * quad;
       if (st < s1 && ncol) {
-        if (WBITS == 8)
-          bw[s] = *reinterpret_cast<const i32x4*>(bt + (int64_t)n * K + k);
-        else
-          bw[s] = unpack16_i4(*reinterpret_cast<const uint2*>(bt + ((int64_t)n * K + k) / 2));
+        bw[s] = *reinterpret_cast<const BRaw*>(bt + ((int64_t)n * K + k) * WBITS / 8);
       } else {
-        bw[s] = i32x4{0, 0, 0, 0};
+        bw[s] = BRaw{};
       }
     }
   };
@@ -181,7 +183,7 @@ skinny_gemm_kernel(const void* __restrict__ a_src, int64_t lda, float clip, cons
           if (ASRC == SK_A_I8 && abits == 8)
             aw[s][rb] = *reinterpret_cast<const i32x4*>(reinterpret_cast<const int8_t*>(a_src) + (int64_t)m * K + k);
           else if (ASRC == SK_A_I8)     // 4-bit codes, two per byte
-            aw[s][rb] = unpack16_i4(*reinterpret_cast<const uint2*>(reinterpret_cast<const uint8_t*>(a_src) +
+            aw[s][rb] = widen16_i4(*reinterpret_cast<const uint2*>(reinterpret_cast<const uint8_t*>(a_src) +
                                                                    ((int64_t)m * K + k) / 2));
           else
             aw[s][rb] = *reinterpret_cast<const i32x4*>(qa + m * qa_ld + k);
@@ -193,9 +195,12 @@ skinny_gemm_kernel(const void* __restrict__ a_src, int64_t lda, float clip, cons
 #pragma unroll
     for (int s = 0; s < kSkBatch; ++s) {
       if (st0 + s >= s1) continue;     // (not break: keeps the register arrays statically indexed)
+      i32x4 bf;
+      if constexpr (WBITS == 8) bf = bw[s];
+      else bf = widen16_i4(bw[s]);
 #pragma unroll
       for (int rb = 0; rb < 2; ++rb)
-        if (rb < rbl) acc[rb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(aw[s][rb], bw[s], acc[rb], 0, 0, 0);
+        if (rb < rbl) acc[rb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(aw[s][rb], bf, acc[rb], 0, 0, 0);
       if (gsteps && ++step_in_group == gsteps) {
         const int g = (st0 + s) / gsteps;
 #pragma unroll
@@ -214,6 +219,7 @@ skinny_gemm_kernel(const void* __restrict__ a_src, int64_t lda, float clip, cons
   __syncthreads();
 
   // --- epilogue: one thread per output (row m, column n) ------------------------
+  const int sh = (WBITS == 4 ? 4 : 0) + (ASRC == SK_A_I8 && abits == 4 ? 4 : 0);
   for (int t = tid; t < M * cols; t += 64 * nw) {
     const int m = t / cols, nl = t % cols;
     const int32_t nn = blockIdx.x * cols + nl;
@@ -225,12 +231,13 @@ skinny_gemm_kernel(const void* __restrict__ a_src, int64_t lda, float clip, cons
     if (!group) {
       int32_t tot = 0;
       for (int ww = 0; ww < nw; ++ww) tot += red[(ww * rbl + rb) * 64 + src][v];
+      tot >>= sh;
       if (dbg) dbg[(int64_t)m * N + nn] = tot;
       y = mul_rn(mul_rn((float)tot, rs), first ? pre_cs : col_scale[nn]);
     } else {
       float S = 0.f;
       for (int g = 0; g < ng; ++g)
-        S = add_rn(S, mul_rn((float)red[(g * rbl + rb) * 64 + src][v], s_gscale[g * kSkCols + nl]));
+        S = add_rn(S, mul_rn((float)(red[(g * rbl + rb) * 64 + src][v] >> sh), s_gscale[g * kSkCols + nl]));
       y = mul_rn(S, rs);
     }
     sk_store(so, m, nn, y);

@@ -265,6 +265,82 @@ absorb_kernel(const _Float16* __restrict__ q, const uint8_t* __restrict__ bt, co
 }
 
 // ---------------------------------------------------------------------------
+// Context chunks.  The (at most 64) sequences' rows are cut into chunks of one
+// length, the smallest multiple of `gran` (whole tiles) with which all of them
+// together make at most `slots` chunks; chunk `ch` of sequence b is slot
+// first(b) + ch.  Found on the device from seq_len, a sequence per lane, so
+// the slots fill the chip also when the lengths differ (with a chunk cut from
+// the longest length alone, 32 sequences of 4224 .. 8192 tokens used 196 of
+// 256 CUs), and a graph replayed over a growing cache cuts it anew.
+// With no more slots than sequences each is one chunk.
+// ---------------------------------------------------------------------------
+// inclusive sum over the lanes below and this one
+__device__ __forceinline__ int lanes_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr 1, 2, 4, 8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast 15, 31
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+  return x;
+}
+
+struct ChunkPlan {
+  int len, upto;   // this lane's sequence: rows, chunks of it and of those before it
+  int chunk;       // (uniform)
+};
+__device__ __forceinline__ ChunkPlan plan_chunks(const int32_t* __restrict__ seq_len, int32_t capacity, int32_t batch,
+                                                 int32_t slots, int32_t gran) {
+  const int lane = threadIdx.x & 63;
+  ChunkPlan p;
+  p.len = lane < batch ? max(min(seq_len[lane], capacity), 0) : 0;
+  // (unsigned: a length plus a chunk, or all the lengths, may pass 2^31)
+  auto pieces = [](uint32_t n, uint32_t c) { return (int)((n + c - 1) / c); };
+  auto up = [&](int x) { return (x + gran - 1) & -gran; };            // gran is a power of two
+  auto total = [](int scan) { return __builtin_amdgcn_readlane(scan, 63); };
+  if (batch == 1) {
+    p.chunk = up(max(pieces(__builtin_amdgcn_readfirstlane(p.len), slots), 1));
+    p.upto = pieces(p.len, p.chunk);
+    return p;
+  }
+  if (slots <= batch) {
+    int m = p.len;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
+    p.chunk = up(max(__builtin_amdgcn_readfirstlane(m), 1));
+    p.upto = lanes_scan(pieces(p.len, p.chunk));
+    return p;
+  }
+  // T / slots rows per chunk at least; T / (slots - batch) are always enough
+  // (sequence ends waste less than one chunk each); a few steps between
+  const uint32_t rows = (uint32_t)total(lanes_scan(p.len));
+  const int lo = pieces(rows, slots);
+  p.chunk = up(max(lo, 1));
+  p.upto = lanes_scan(pieces(p.len, p.chunk));
+  if (total(p.upto) > slots) {
+    const int step = max(gran, up((pieces(rows, slots - batch) - lo) / 8));
+    do {
+      p.chunk += step;
+      p.upto = lanes_scan(pieces(p.len, p.chunk));
+    } while (total(p.upto) > slots);
+  }
+  return p;
+}
+
+// The sequence of a slot (batch: none), its length and the chunk's number in it.
+struct SlotChunk {
+  int b, len, ch;
+};
+__device__ __forceinline__ SlotChunk slot_chunk(const ChunkPlan& p, int32_t batch, int slot) {
+  const int lane = threadIdx.x & 63;
+  SlotChunk o;
+  o.b = __builtin_amdgcn_readfirstlane((int)__popcll(__ballot(lane < batch && p.upto <= slot)));
+  o.len = __builtin_amdgcn_readlane(p.len, o.b & 63);
+  o.ch = slot - (o.b > 0 ? __builtin_amdgcn_readlane(p.upto, (o.b - 1) & 63) : 0);
+  return o;
+}
+
+// ---------------------------------------------------------------------------
 // Latent attention over one context chunk of one sequence.
 //
 // The workgroup has NW waves; wave w owns latent columns [w*RW, (w+1)*RW).
@@ -287,7 +363,7 @@ template <int RW, int NW, int FMT, bool PRE>
 __global__ void __launch_bounds__(NW * 64)
 latent_attn_kernel(const _Float16* __restrict__ qt, const uint8_t* __restrict__ cdata,
                    const float* __restrict__ cscale, const int32_t* __restrict__ seq_len,
-                   int32_t capacity, int32_t r, int32_t chunk, int32_t n_chunks, int32_t q_len,
+                   int32_t capacity, int32_t r, int32_t batch, int32_t slots, int32_t gran, int32_t q_len,
                    const float* __restrict__ pre, _Float16* __restrict__ o_part, float* __restrict__ ml_part) {
   constexpr int KS = RW / 16;    // 16-wide contraction steps of the score MFMA
   constexpr int RB = RW / 32;    // 32-row blocks of the output MFMA
@@ -309,13 +385,16 @@ latent_attn_kernel(const _Float16* __restrict__ qt, const uint8_t* __restrict__ 
   // tokens whose scores it holds).
   float* scl = reinterpret_cast<float*>(smem + NW * 32 * CST * 2 + (PRE ? 0 : (size_t)(NW + 1) * 1024 * 4)) + w * 32;
 
-  // Workgroup row blockIdx.y is query i of sequence b (q_len queries per
-  // sequence, the last q_len cached positions): it sees positions
+  // Workgroup (slot, query i): query i of the slot's sequence b (q_len queries
+  // per sequence, the last q_len cached positions) sees positions
   // [0, L - q_len + i], causally.  Decode has q_len = 1.
-  const int vb = blockIdx.y, ch = blockIdx.x;
-  const int b = vb / q_len, qi = vb - b * q_len;
-  const int L = min(seq_len[b], capacity) - (q_len - 1 - qi);
-  const int t_begin = ch * chunk;
+  const int qi = blockIdx.y;
+  const ChunkPlan plan = plan_chunks(seq_len, capacity, batch, slots, gran);
+  const SlotChunk sc = slot_chunk(plan, batch, blockIdx.x);
+  if (sc.b >= batch) return;
+  const int b = sc.b, vb = b * q_len + qi, chunk = plan.chunk;
+  const int L = sc.len - (q_len - 1 - qi);
+  const int t_begin = sc.ch * chunk;
   if (t_begin >= L) return;
   const int t_end = min(L, t_begin + chunk);
   const int slice0 = w * RW;
@@ -670,7 +749,7 @@ latent_attn_kernel(const _Float16* __restrict__ qt, const uint8_t* __restrict__ 
   }
   }
 
-  const int64_t part = (int64_t)vb * n_chunks + ch;
+  const int64_t part = (int64_t)qi * slots + blockIdx.x;
   if (w == 0 && lane < 32) {
     ml_part[part * 64 + l32] = m_run;
     ml_part[part * 64 + 32 + l32] = l_run;
@@ -962,7 +1041,7 @@ template <int UMAX, int FMT>
 __global__ void __launch_bounds__(kH16Waves * 64)
 latent_attn_h16_kernel(const _Float16* __restrict__ qt, const uint8_t* __restrict__ cdata,
                        const float* __restrict__ cscale, const int32_t* __restrict__ seq_len,
-                       int32_t capacity, int32_t r, int32_t hp, int32_t chunk, int32_t n_chunks,
+                       int32_t capacity, int32_t r, int32_t hp, int32_t batch, int32_t slots, int32_t gran,
                        int32_t q_len, _Float16* __restrict__ o_part, float* __restrict__ ml_part) {
   constexpr int NW = kH16Waves, NB = H16Blocks<UMAX>::value;
   constexpr int CST = 128 * UMAX + 24;
@@ -974,8 +1053,8 @@ latent_attn_h16_kernel(const _Float16* __restrict__ qt, const uint8_t* __restric
   f32x4* ssum = spart + NB * NW * 64;
 
   const int n_hb = hp >> 4;
-  // Workgroup -> (sequence-query row vb, head block hb, chunk ch).  The n_hb
-  // head blocks of one (vb, ch) read the same cache rows, so they get ids
+  // Workgroup -> (query qi, head block hb, slot).  The n_hb head blocks of one
+  // (qi, slot) read the same cache rows, so they get ids
   // that one XCD receives together (the chip dispatches the i-th workgroup,
   // x fastest, to XCD i % 8) and share its L2 instead of each XCD fetching
   // the rows again.  A bijection on the grid.
@@ -990,10 +1069,13 @@ latent_attn_h16_kernel(const _Float16* __restrict__ qt, const uint8_t* __restric
     pair = lin / n_hb;
     hb = lin % n_hb;
   }
-  const int vb = pair / n_launch, ch = pair % n_launch, row = vb * n_hb + hb;
-  const int b = vb / q_len, qi = vb - b * q_len;
-  const int L = min(seq_len[b], capacity) - (q_len - 1 - qi);
-  const int t_begin = ch * chunk;
+  const int qi = pair / n_launch, slot = pair % n_launch;
+  const ChunkPlan plan = plan_chunks(seq_len, capacity, batch, slots, gran);
+  const SlotChunk sc = slot_chunk(plan, batch, slot);
+  if (sc.b >= batch) return;
+  const int b = sc.b, vb = b * q_len + qi, chunk = plan.chunk;
+  const int L = sc.len - (q_len - 1 - qi);
+  const int t_begin = sc.ch * chunk;
   if (t_begin >= L) return;
   const int t_end = min(L, t_begin + chunk);
   // this wave's latent units [u0, u0 + nu) of 128 columns: nu is UMAX or UMAX - 1
@@ -1002,7 +1084,7 @@ latent_attn_h16_kernel(const _Float16* __restrict__ qt, const uint8_t* __restric
   const int slice0 = 128 * u0;
   const int l16 = lane & 15;
   const _Float16* qrow = qt + ((int64_t)vb * hp + hb * 16 + l16) * r + slice0;
-  const int64_t part = (int64_t)row * n_chunks + ch;
+  const int64_t part = (int64_t)(qi * n_hb + hb) * slots + slot;
   _Float16* op = o_part + part * (int64_t)r * 16;
   float* mlp = ml_part + part * 32;
   const int64_t seq_row0 = (int64_t)b * capacity;
@@ -1015,8 +1097,8 @@ latent_attn_h16_kernel(const _Float16* __restrict__ qt, const uint8_t* __restric
 }
 
 // ---------------------------------------------------------------------------
-// Merge the chunk partials of the latent form.  The attention grid row
-// (sequence-query row vb, head block hb) of HB heads holds, per chunk c,
+// Merge the chunk partials of the latent form.  For a (sequence, query) row vb
+// and head block hb of HB heads there are, per chunk c of its sequence,
 // m_c, l_c per head and the normalized O_c / l_c as fp16 in the [x/4][HB][4]
 // order the attention kernels write.  With m = max m_c and
 // w_c = 2^(m_c - m) l_c / sum, the result O[vb][h][x] = sum_c w_c (O_c / l_c)[h][x]
@@ -1036,17 +1118,21 @@ constexpr int kMergeBatch = 16;   // chunk partials in flight per thread (one ro
 template <int HB, int CG>
 __global__ void __launch_bounds__(256)
 merge_latent_kernel(const _Float16* __restrict__ o_part, const float* __restrict__ ml_part,
-                    const int32_t* __restrict__ seq_len, int32_t capacity, int32_t chunk, int32_t n_chunks,
-                    int32_t n_launched, int32_t q_len, int32_t r, int32_t hp, _Float16* __restrict__ o_lat) {
+                    const int32_t* __restrict__ seq_len, int32_t capacity, int32_t batch, int32_t slots,
+                    int32_t gran, int32_t n_launched, int32_t q_len, int32_t r, int32_t hp,
+                    _Float16* __restrict__ o_lat) {
   constexpr int LPH = 256 / HB;      // lanes per head in the weights phase
   constexpr int ELEMS = kMergeElems / CG, TPG = 256 / CG;   // elements per workgroup, threads per group
   __shared__ float wgt[kMaxChunks * HB];
   const int n_hb = hp / HB;
   const int row = blockIdx.y, vb = row / n_hb, hb = row - vb * n_hb, tid = threadIdx.x;
   const int cg = tid / TPG, gt = tid % TPG;
-  const int L = min(seq_len[vb / q_len], capacity) - (q_len - 1 - vb % q_len);
-  const int nv = L > 0 ? min(min((L + chunk - 1) / chunk, n_launched), kMaxChunks) : 0;
-  const int64_t pb = (int64_t)row * n_chunks;
+  const int b = vb / q_len, qi = vb - b * q_len;
+  const ChunkPlan plan = plan_chunks(seq_len, capacity, batch, slots, gran);
+  const int L = __builtin_amdgcn_readlane(plan.len, b) - (q_len - 1 - qi);
+  const int first = b > 0 ? __builtin_amdgcn_readlane(plan.upto, b - 1) : 0;
+  const int nv = L > 0 ? min(min((L + plan.chunk - 1) / plan.chunk, n_launched - first), kMaxChunks) : 0;
+  const int64_t pb = (int64_t)(qi * n_hb + hb) * slots + first;
   // element e8 (8 halves): latent quad x4 = e8 / (HB / 2), heads 2*(e8 % (HB / 2)) and +1;
   // the first batch of partial loads goes out before the weights are known
   const int64_t e0 = (int64_t)blockIdx.x * ELEMS + 8 * gt;
@@ -1287,7 +1373,8 @@ struct AbsorbPlan {
   int n_hb, hp;      // head blocks per row and padded heads per row (n_hb * hb)
   int rw, nw;        // 32-head kernel: latent columns per wave, waves
   int umax;          // 16-head kernel: 128-column units per wave (at most)
-  int chunk, n_chunks, n0;
+  int n0, slots, gran;      // chunks per row on average, slots of one query and head block, chunk granularity
+  int n_launched;           // slots that can be in use at max_len
   size_t qt_bytes, opart_bytes, ml_bytes, olat_bytes;
 };
 
@@ -1324,13 +1411,11 @@ static AbsorbPlan plan_absorbed(const qsvd_layer& w, const qsvd_cache& c, int32_
   // blocks (one workgroup per CU): at most one round
   p.n0 = p.hb == kHeadBlk ? target_chunks((int)grows) : (int)(grows >= 256 ? 1 : 256 / grows);
   const int len = c.max_len > 0 ? c.max_len : 1;
-  int ch = (len + p.n0 - 1) / p.n0;
   // whole tiles (16-head plans: and ring rounds): half a tile costs a whole
   // one's time and a partial more to merge
-  const int gran = p.hb == kHeadBlk ? 32 : 64;
-  ch = ((ch + gran - 1) / gran) * gran;
-  p.chunk = ch;
-  p.n_chunks = (len + ch - 1) / ch;
+  p.gran = p.hb == kHeadBlk ? 32 : 64;
+  p.slots = std::min(c.batch * p.n0, kMaxChunks);
+  p.n_launched = (int)std::min<int64_t>(p.slots, (int64_t)c.batch * ((len + p.gran - 1) / p.gran));
   p.qt_bytes = (size_t)rows * p.hp * w.r * sizeof(_Float16);
   p.opart_bytes = (size_t)grows * p.n0 * w.r * p.hb * sizeof(_Float16);
   p.ml_bytes = (size_t)grows * p.n0 * 2 * p.hb * sizeof(float);
@@ -1365,9 +1450,9 @@ static hipError_t launch_latent(const AbsorbPlan& p, const qsvd_cache& c, int32_
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   KernelScope ks("latent_attn", s);
-  QSVD_LAUNCH(ks, kern, dim3(p.n_chunks, c.batch * q_len), dim3(NW * 64), lds, s, qt,
-                     (const uint8_t*)c.data, c.scale, c.seq_len, c.capacity, c.r, p.chunk,
-                     p.n0, q_len, pre, opart, ml);
+  QSVD_LAUNCH(ks, kern, dim3(p.n_launched, q_len), dim3(NW * 64), lds, s, qt,
+                     (const uint8_t*)c.data, c.scale, c.seq_len, c.capacity, c.r, c.batch, p.slots,
+                     p.gran, q_len, pre, opart, ml);
   return hipGetLastError();
 }
 
@@ -1379,8 +1464,9 @@ static hipError_t launch_latent_h16(const AbsorbPlan& p, const qsvd_cache& c, in
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   KernelScope ks("latent_attn_h16", s);
-  QSVD_LAUNCH(ks, kern, dim3(p.n_chunks, c.batch * q_len * p.n_hb), dim3(kH16Waves * 64), lds, s, qt,
-              (const uint8_t*)c.data, c.scale, c.seq_len, c.capacity, c.r, p.hp, p.chunk, p.n0, q_len, opart, ml);
+  QSVD_LAUNCH(ks, kern, dim3(p.n_launched, q_len * p.n_hb), dim3(kH16Waves * 64), lds, s, qt,
+              (const uint8_t*)c.data, c.scale, c.seq_len, c.capacity, c.r, p.hp, c.batch, p.slots, p.gran, q_len,
+              opart, ml);
   return hipGetLastError();
 }
 
@@ -1465,8 +1551,8 @@ static hipError_t launch_merge_groups(const AttnArgs& a, const AbsorbPlan& p, in
   const qsvd_cache& c = *a.c;
   KernelScope ks("merge_latent", s);
   const dim3 grid((a.w->r * HB + kMergeElems / CG - 1) / (kMergeElems / CG), rows * p.n_hb);
-  QSVD_LAUNCH(ks, (merge_latent_kernel<HB, CG>), grid, dim3(256), 0, s, opart, ml, c.seq_len, c.capacity, p.chunk,
-              p.n0, p.n_chunks, a.q_len, a.w->r, p.hp, olat);
+  QSVD_LAUNCH(ks, (merge_latent_kernel<HB, CG>), grid, dim3(256), 0, s, opart, ml, c.seq_len, c.capacity,
+              c.batch, p.slots, p.gran, p.n_launched, a.q_len, a.w->r, p.hp, olat);
   return hipGetLastError();
 }
 
@@ -1477,9 +1563,11 @@ static hipError_t launch_merge_groups(const AttnArgs& a, const AbsorbPlan& p, in
 template <int HB>
 static hipError_t launch_merge(const AttnArgs& a, const AbsorbPlan& p, int32_t rows, const _Float16* opart,
                                const float* ml, _Float16* olat, hipStream_t s) {
+  const qsvd_cache& c = *a.c;
   const int64_t wgs = (int64_t)((a.w->r * HB + kMergeElems - 1) / kMergeElems) * rows * p.n_hb;
-  if (wgs <= 64 && p.n_chunks >= 8) return launch_merge_groups<HB, 8>(a, p, rows, opart, ml, olat, s);
-  if (wgs <= 128 && p.n_chunks >= 8) return launch_merge_groups<HB, 4>(a, p, rows, opart, ml, olat, s);
+  const int per_seq = p.n_launched / c.batch;      // chunks of a sequence, on average at most
+  if (wgs <= 64 && per_seq >= 8) return launch_merge_groups<HB, 8>(a, p, rows, opart, ml, olat, s);
+  if (wgs <= 128 && per_seq >= 8) return launch_merge_groups<HB, 4>(a, p, rows, opart, ml, olat, s);
   return launch_merge_groups<HB, 1>(a, p, rows, opart, ml, olat, s);
 }
 

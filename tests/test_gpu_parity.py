@@ -1344,6 +1344,36 @@ def test_prefill_attention_wide_int4(fmt=O.CACHE_I4):
     assert ok, info
 
 
+@pytest.mark.parametrize("lengths,q_len", [
+    ([1], 1), ([33], 1),                                     # a single row; one past a tile
+    ([2000, 1, 1, 1], 1),                                    # one sequence takes nearly every chunk
+    ([0, 700, 0, 64, 0], 1),                                 # empty sequences between
+    ([31 + 13 * i for i in range(64)], 1),                   # the most sequences, four chunks each on average
+    ([40 + 29 * i for i in range(20)], 13),                  # more query rows than CUs: one chunk a sequence
+    ([300, 5, 900], 7),                                      # several queries, one sequence shorter than the block
+], ids=["one", "tile1", "skewed", "empty", "b64", "rows260", "q7"])
+@pytest.mark.parametrize("hq", [8, 40], ids=["h32blk", "h16blk"])
+def test_decode_chunks_over_ragged_lengths(lengths, q_len, hq):
+    """The absorbed form's context chunks, cut on the device from the lengths,
+    where the cut has its edges, for both head-block kernels, against the
+    oracle; queries without a visible position are zeros."""
+    L = configs.LayerShape(d=256, n_q_heads=hq, n_kv_heads=8, head_dim=64, r=128)
+    ol, dl = _random_factor_layer(L, 1500 + hq)
+    wl = configs.Workload(97, "chunks", L, "gaussian", 8, 0, 8, O.CACHE_I8)
+    oc, dc = _prefilled_caches(wl, O.CACHE_I8, lengths, max(lengths) + 5)
+    B_ = len(lengths)
+    q = (np.random.default_rng(hq + B_).standard_normal((B_, q_len, hq * 64)) * 4.0).astype(np.float16)
+    ref = np.zeros(q.shape, np.float64)
+    for b, n in enumerate(lengths):
+        k = min(q_len, n)
+        if k:
+            ref[b:b + 1, q_len - k:] = O.attention_reference(ol, oc, q.astype(np.float64)[:, q_len - k:], q_len=k,
+                                                             batches=[b])[b:b + 1]
+    H.say(f"decode chunks heads={hq} lengths={lengths[:6]} q_len={q_len}")
+    out = H.host(H.decode_attention(dl, dc, H.dev(q), B.QSVD_ATTN_ABSORBED, q_len=q_len))
+    _check_qlen_block(out.reshape(q.shape), ref, lengths, q_len)
+
+
 def test_decode_gqa_int4_cache_ragged(gqa):
     """Int4 latent cache (4-bit per-token codes of C with fp32 scales, two codes
     per byte): ragged prior lengths 3 / 50 / 97 of synthetic rows, then 3 decode

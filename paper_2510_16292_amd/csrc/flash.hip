@@ -200,7 +200,7 @@ prefill_flash_kernel(const _Float16* __restrict__ q, const _Float16* __restrict_
     q_off = nk - nq;
   } else {
     q_row0 = k_row0 = cu[b];
-    nq = nk = cu[b + 1] - q_row0;
+    nq = nk = min(cu[b + 1] - q_row0, ca.q_len);     // (q_len: the launch's longest sequence)
     q_off = 0;
   }
   const int first = wg * UW / G * kFaQW;                        // first query of the workgroup
@@ -224,7 +224,7 @@ prefill_flash_kernel(const _Float16* __restrict__ q, const _Float16* __restrict_
     if (tid < DH / 2) {
       const double f = exp2(-2.0 * tid / DH * log2_theta);
       freq[tid] = f * 0.15915494309189533576888376337251;
-      if (ROPE) {
+      if (ROPE && n_tiles > 1) {
         double rev = (double)kFaK * freq[tid];
         rev -= floor(rev);
         float sn, cs;
@@ -534,19 +534,30 @@ static hipError_t launch_flash(const PrefillAttnArgs& a, const FaCacheArgs& ca, 
 
 bool prefill_attention_supported(int32_t head_dim) { return head_dim == 64 || head_dim == 128; }
 
+// At most half the CUs get 128 queries of a head: then the waves' own latency
+// counts, and prompts of up to 512 tokens take the kernel with shorter chains.
+static bool few_workgroups(const PrefillAttnArgs& a) {
+  return (int64_t)a.batch * a.n_q_heads * ((a.max_seqlen + 127) / 128) <= 128;
+}
+
 template <int DH>
 static hipError_t launch_prefill(const PrefillAttnArgs& a, hipStream_t s) {
-  const FaCacheArgs none{};
+  FaCacheArgs none{};
+  none.q_len = a.max_seqlen;                // rows past it are left alone
   // Rotary layers turn the keys once per workgroup, so eight waves take eight
   // units.  Without that, four: the two workgroups of a CU cover each other's
   // barriers (four units in two shares of the keys, eight waves: 41 us for the
   // 4 x 640 prompts, against 28.5).
   if (a.rope_theta > 0.f) return launch_flash<DH, FA_ROPE, false, 8, 1>(a, none, s);
+  // (Long prompts of few heads have too few workgroups for two per CU, and
+  // there the shares halve the longest one: 1500 tokens of 4 heads 27.3, 21.0 us.)
+  if (few_workgroups(a)) return launch_flash<DH, FA_PLAIN, false, 8, 2>(a, none, s);
   return launch_flash<DH, FA_PLAIN, false, 4, 1>(a, none, s);
 }
 
 hipError_t launch_prefill_attention(const PrefillAttnArgs& a, hipStream_t s) {
   if (a.batch == 0 || a.max_seqlen == 0) return hipSuccess;
+  if (few_workgroups(a) && a.max_seqlen <= 512) return launch_prefill_attention_short(a, s);
   return a.head_dim == 128 ? launch_prefill<128>(a, s) : launch_prefill<64>(a, s);
 }
 

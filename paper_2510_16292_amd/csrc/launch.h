@@ -161,6 +161,8 @@ struct PrefillAttnArgs {
 };
 bool prefill_attention_supported(int32_t head_dim);
 hipError_t launch_prefill_attention(const PrefillAttnArgs& a, hipStream_t s);
+// ... of short prompts that make few workgroups (chosen by launch_prefill_attention).
+hipError_t launch_prefill_attention_short(const PrefillAttnArgs& a, hipStream_t s);
 
 struct CacheAttnArgs {
   const _Float16* q;        // [batch][q_len][n_q_heads * head_dim]

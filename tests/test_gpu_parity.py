@@ -651,11 +651,13 @@ def test_prefill_attention_rope_ragged(shape, lengths, theta):
 
 @pytest.mark.parametrize("theta", [None, 1e4], ids=["plain", "rope"])
 @pytest.mark.parametrize("shape,lengths", [
-    ((3, 1, 64), [31, 32, 33, 63, 64, 65, 1]),   # units of 32 queries and tiles of 64 keys at their edges, one odd group each
-    ((7, 1, 128), [97, 256, 257]),               # seven heads of a group over workgroups of four and eight units
+    ((3, 1, 64), [31, 32, 33, 63, 64, 65, 1]),   # the short-prompt kernel: 16-query blocks and 64-key tiles at their edges
+    ((7, 1, 128), [97, 128, 129]),
+    ((3, 1, 64), 8 * [31, 32, 33, 63, 64, 65, 1]),   # units of 32 queries and tiles at their edges, one odd group each
+    ((7, 1, 128), 7 * [97, 256, 257]),           # seven heads of a group over workgroups of four and eight units
     ((5, 5, 128), [513, 575]),                   # past the eighth tile (the keys' exact angles are formed anew)
     ((2, 2, 64), [9] * 70),                      # more (sequence, head) groups than one set of an XCD holds
-], ids=["g3-dh64", "g7-dh128", "mha5-resync", "many-short"])
+], ids=["short-g3", "short-g7", "g3-dh64", "g7-dh128", "mha5-resync", "many-short"])
 def test_prefill_attention_unit_edges(shape, lengths, theta):
     """Prefill attention where its units (32 queries of a head), key tiles,
     workgroups and workgroup order have their edges, against the oracle."""
@@ -667,6 +669,25 @@ def test_prefill_attention_unit_edges(shape, lengths, theta):
     ok, info = H.close_enough(out, want)
     H.say(f"  max-abs, rel-L2, rms = {info}")
     assert ok, info
+
+
+@pytest.mark.parametrize("theta", [None, 1e4], ids=["plain", "rope"])
+def test_prefill_attention_past_max_seqlen(theta):
+    """Rows past max_seqlen stay as they were, the rows before it do not see them."""
+    hq, hkv, dh, n, most = 4, 4, 64, 200, 70
+    Q, K, V = _qkv(395, n, hq, hkv, dh)
+    q, k, v = H.dev(Q), H.dev(K), H.dev(V)
+    full = H.host(H.prefill_attention(q, k, v, [n], hq, hkv, dh, rope_theta=theta))
+    out = H.dev(np.full((n, hq * dh), 7.0, np.float16))
+    cu = H.dev(np.array([0, n], np.int32))
+    args = (B.ptr(q), B.ptr(k), B.ptr(v), 1, B.ptr(cu), most, hq, hkv, dh, 0.0)
+    if theta:
+        B.check(B.qsvd_prefill_attention_rope(*args, theta, B.ptr(out), B.stream_handle()))
+    else:
+        B.check(B.qsvd_prefill_attention(*args, B.ptr(out), B.stream_handle()))
+    got = H.host(out)
+    assert H.close_enough(got[:most], full[:most])[0]
+    assert np.all(got[most:] == 7.0)
 
 
 def test_prefill_attention_rope_llava7b_full():

@@ -346,7 +346,7 @@ prefill_flash_kernel(const _Float16* __restrict__ q, const _Float16* __restrict_
   for (int i = 0; i < n_rounds; ++i) {
     const int t = KSP * i + share;
     uint8_t* buf = fa_smem + buffer(i);
-    // this round's tiles have landed and every wave is done with the round
+    // these tiles have landed and every wave is done with the ones
     // before, whose buffers take the next
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     const bool more = t + KSP < n_tiles;

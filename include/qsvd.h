@@ -264,6 +264,11 @@ qsvd_status qsvd_prefill_attention_rope(const void* q, const void* k, const void
  * products, I8 on the int8 products, I4 on the 4-bit products), and with
  * q_len > 1 (causal attention of the last q_len positions over the rebuilt
  * rows on the fp16 matrix cores) head_dim 64 or 128.
+ * The absorbed form sums a sequence's rows in chunks, whose partial sums are
+ * rounded to fp16.  How long they are follows from max_len and the batch size
+ * where all lengths need equally many chunks, else from all the lengths: the
+ * low-order bits of a sequence's output may then differ with the lengths of
+ * the other sequences.  A call repeats exactly for the same arguments.
  * Launch grids are sized from the host c->max_len and every length is read
  * from seq_len on the device, so a call may be captured in a graph and
  * replayed while the cache grows, provided c->max_len at capture is at least

@@ -266,14 +266,30 @@ absorb_kernel(const _Float16* __restrict__ q, const uint8_t* __restrict__ bt, co
 
 // ---------------------------------------------------------------------------
 // Context chunks.  The (at most 64) sequences' rows are cut into chunks of one
-// length, the smallest multiple of `gran` (whole tiles) with which all of them
-// together make at most `slots` chunks; chunk `ch` of sequence b is slot
-// first(b) + ch.  Found on the device from seq_len, a sequence per lane, so
-// the slots fill the chip also when the lengths differ (with a chunk cut from
-// the longest length alone, 32 sequences of 4224 .. 8192 tokens used 196 of
-// 256 CUs), and a graph replayed over a growing cache cuts it anew.
-// With no more slots than sequences each is one chunk.
+// length, whole multiples of `gran` rows; chunk `ch` of sequence b is slot
+// first(b) + ch.
+//
+// Where every sequence needs as many chunks as the longest possible one
+// (max_len rows in n_even chunks of `even` rows), that cut, which the host
+// makes, is taken: one comparison per sequence.  Otherwise the cut is found
+// from all the lengths, a sequence per lane, so that the slots fill the chip
+// also when they differ (with the host's cut alone, 32 sequences of 4224 ..
+// 8192 tokens used 196 of 256 CUs), and a graph replayed over a growing cache
+// cuts it anew: T rows in all, chunks of T / (slots - batch / 2) rows first
+// (a sequence's last chunk is half empty on average), then at most two larger
+// lengths, the second T / (slots - batch), which always makes at most `slots`
+// chunks; never more than the host's.  The smallest length that fits may be up
+// to a step below the one found: not searched for, since every workgroup waits
+// for the cut before its first cache address (a search over exact lengths
+// took 0.5 .. 1 us per launch, twice per call).
 // ---------------------------------------------------------------------------
+struct ChunkCut {
+  int32_t batch, stride;            // sequences, slots of one query and head block in the partials
+  int32_t slots, gran;              // slots of the cut from all lengths, its chunks' granularity
+  int32_t even, n_even, even_lo;    // the host's cut; it serves lengths in (even_lo, even * n_even]
+  float inv_mid, inv_step;          // rows -> first chunk length, half the way from there to the last
+};
+
 // inclusive sum over the lanes below and this one
 __device__ __forceinline__ int lanes_scan(int x) {
   x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr 1, 2, 4, 8
@@ -285,45 +301,35 @@ __device__ __forceinline__ int lanes_scan(int x) {
   return x;
 }
 
+// ceil(n / c) for results up to a few hundred: the quotient by the reciprocal
+// is within one of the exact one, and the remainder decides.
+__device__ __forceinline__ int chunks_of(int n, int c) {
+  const int q = (int)((float)n * __builtin_amdgcn_rcpf((float)c)), rem = n - q * c;
+  return q + (rem > 0) + (rem > c);
+}
+
 struct ChunkPlan {
   int len, upto;   // this lane's sequence: rows, chunks of it and of those before it
   int chunk;       // (uniform)
 };
-__device__ __forceinline__ ChunkPlan plan_chunks(const int32_t* __restrict__ seq_len, int32_t capacity, int32_t batch,
-                                                 int32_t slots, int32_t gran) {
+__device__ __forceinline__ ChunkPlan plan_chunks(const int32_t* __restrict__ seq_len, int32_t capacity,
+                                                 const ChunkCut& c) {
   const int lane = threadIdx.x & 63;
   ChunkPlan p;
-  p.len = lane < batch ? max(min(seq_len[lane], capacity), 0) : 0;
-  // (unsigned: a length plus a chunk, or all the lengths, may pass 2^31)
-  auto pieces = [](uint32_t n, uint32_t c) { return (int)((n + c - 1) / c); };
-  auto up = [&](int x) { return (x + gran - 1) & -gran; };            // gran is a power of two
-  auto total = [](int scan) { return __builtin_amdgcn_readlane(scan, 63); };
-  if (batch == 1) {
-    p.chunk = up(max(pieces(__builtin_amdgcn_readfirstlane(p.len), slots), 1));
-    p.upto = pieces(p.len, p.chunk);
-    return p;
+  p.len = lane < c.batch ? max(min(seq_len[lane], capacity), 0) : 0;
+  p.chunk = c.even;
+  p.upto = (lane + 1) * c.n_even;
+  if (!__any(lane < c.batch && (p.len <= c.even_lo || p.len > c.even * c.n_even))) return p;
+  const float rows = (float)(uint32_t)__builtin_amdgcn_readlane(lanes_scan(p.len), 63);
+  // (gran is a power of two; at least one gran)
+  auto up = [&](float x) { return (max((int)__builtin_ceilf(x), 1) + c.gran - 1) & -c.gran; };
+  const int step = up(rows * c.inv_step);
+  for (p.chunk = up(rows * c.inv_mid); p.chunk < c.even; p.chunk += step) {
+    p.upto = lanes_scan(chunks_of(p.len, p.chunk));
+    if (__builtin_amdgcn_readlane(p.upto, 63) <= c.slots) return p;
   }
-  if (slots <= batch) {
-    int m = p.len;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
-    p.chunk = up(max(__builtin_amdgcn_readfirstlane(m), 1));
-    p.upto = lanes_scan(pieces(p.len, p.chunk));
-    return p;
-  }
-  // T / slots rows per chunk at least; T / (slots - batch) are always enough
-  // (sequence ends waste less than one chunk each); a few steps between
-  const uint32_t rows = (uint32_t)total(lanes_scan(p.len));
-  const int lo = pieces(rows, slots);
-  p.chunk = up(max(lo, 1));
-  p.upto = lanes_scan(pieces(p.len, p.chunk));
-  if (total(p.upto) > slots) {
-    const int step = max(gran, up((pieces(rows, slots - batch) - lo) / 8));
-    do {
-      p.chunk += step;
-      p.upto = lanes_scan(pieces(p.len, p.chunk));
-    } while (total(p.upto) > slots);
-  }
+  p.chunk = c.even;
+  p.upto = lanes_scan(chunks_of(p.len, p.chunk));
   return p;
 }
 
@@ -363,7 +369,7 @@ template <int RW, int NW, int FMT, bool PRE>
 __global__ void __launch_bounds__(NW * 64)
 latent_attn_kernel(const _Float16* __restrict__ qt, const uint8_t* __restrict__ cdata,
                    const float* __restrict__ cscale, const int32_t* __restrict__ seq_len,
-                   int32_t capacity, int32_t r, int32_t batch, int32_t slots, int32_t gran, int32_t q_len,
+                   int32_t capacity, int32_t r, ChunkCut cut, int32_t q_len,
                    const float* __restrict__ pre, _Float16* __restrict__ o_part, float* __restrict__ ml_part) {
   constexpr int KS = RW / 16;    // 16-wide contraction steps of the score MFMA
   constexpr int RB = RW / 32;    // 32-row blocks of the output MFMA
@@ -389,9 +395,9 @@ latent_attn_kernel(const _Float16* __restrict__ qt, const uint8_t* __restrict__ 
   // per sequence, the last q_len cached positions) sees positions
   // [0, L - q_len + i], causally.  Decode has q_len = 1.
   const int qi = blockIdx.y;
-  const ChunkPlan plan = plan_chunks(seq_len, capacity, batch, slots, gran);
-  const SlotChunk sc = slot_chunk(plan, batch, blockIdx.x);
-  if (sc.b >= batch) return;
+  const ChunkPlan plan = plan_chunks(seq_len, capacity, cut);
+  const SlotChunk sc = slot_chunk(plan, cut.batch, blockIdx.x);
+  if (sc.b >= cut.batch) return;
   const int b = sc.b, vb = b * q_len + qi, chunk = plan.chunk;
   const int L = sc.len - (q_len - 1 - qi);
   const int t_begin = sc.ch * chunk;
@@ -749,7 +755,7 @@ latent_attn_kernel(const _Float16* __restrict__ qt, const uint8_t* __restrict__ 
   }
   }
 
-  const int64_t part = (int64_t)qi * slots + blockIdx.x;
+  const int64_t part = (int64_t)qi * cut.stride + blockIdx.x;
   if (w == 0 && lane < 32) {
     ml_part[part * 64 + l32] = m_run;
     ml_part[part * 64 + 32 + l32] = l_run;
@@ -1041,8 +1047,8 @@ template <int UMAX, int FMT>
 __global__ void __launch_bounds__(kH16Waves * 64)
 latent_attn_h16_kernel(const _Float16* __restrict__ qt, const uint8_t* __restrict__ cdata,
                        const float* __restrict__ cscale, const int32_t* __restrict__ seq_len,
-                       int32_t capacity, int32_t r, int32_t hp, int32_t batch, int32_t slots, int32_t gran,
-                       int32_t q_len, _Float16* __restrict__ o_part, float* __restrict__ ml_part) {
+                       int32_t capacity, int32_t r, int32_t hp, ChunkCut cut, int32_t q_len,
+                       _Float16* __restrict__ o_part, float* __restrict__ ml_part) {
   constexpr int NW = kH16Waves, NB = H16Blocks<UMAX>::value;
   constexpr int CST = 128 * UMAX + 24;
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -1070,9 +1076,9 @@ latent_attn_h16_kernel(const _Float16* __restrict__ qt, const uint8_t* __restric
     hb = lin % n_hb;
   }
   const int qi = pair / n_launch, slot = pair % n_launch;
-  const ChunkPlan plan = plan_chunks(seq_len, capacity, batch, slots, gran);
-  const SlotChunk sc = slot_chunk(plan, batch, slot);
-  if (sc.b >= batch) return;
+  const ChunkPlan plan = plan_chunks(seq_len, capacity, cut);
+  const SlotChunk sc = slot_chunk(plan, cut.batch, slot);
+  if (sc.b >= cut.batch) return;
   const int b = sc.b, vb = b * q_len + qi, chunk = plan.chunk;
   const int L = sc.len - (q_len - 1 - qi);
   const int t_begin = sc.ch * chunk;
@@ -1084,7 +1090,7 @@ latent_attn_h16_kernel(const _Float16* __restrict__ qt, const uint8_t* __restric
   const int slice0 = 128 * u0;
   const int l16 = lane & 15;
   const _Float16* qrow = qt + ((int64_t)vb * hp + hb * 16 + l16) * r + slice0;
-  const int64_t part = (int64_t)(qi * n_hb + hb) * slots + slot;
+  const int64_t part = (int64_t)(qi * n_hb + hb) * cut.stride + slot;
   _Float16* op = o_part + part * (int64_t)r * 16;
   float* mlp = ml_part + part * 32;
   const int64_t seq_row0 = (int64_t)b * capacity;
@@ -1114,25 +1120,26 @@ latent_attn_h16_kernel(const _Float16* __restrict__ qt, const uint8_t* __restric
 // ---------------------------------------------------------------------------
 constexpr int kMergeElems = 2048;
 constexpr int kMergeBatch = 16;   // chunk partials in flight per thread (one round trip for <= 16 chunks)
+constexpr int kMergeWBatch = 4;   // (m, l) pairs in flight per lane in the weights phase
 
 template <int HB, int CG>
 __global__ void __launch_bounds__(256)
 merge_latent_kernel(const _Float16* __restrict__ o_part, const float* __restrict__ ml_part,
-                    const int32_t* __restrict__ seq_len, int32_t capacity, int32_t batch, int32_t slots,
-                    int32_t gran, int32_t n_launched, int32_t q_len, int32_t r, int32_t hp,
+                    const int32_t* __restrict__ seq_len, int32_t capacity, ChunkCut cut, int32_t n_launched,
+                    int32_t q_len, int32_t r, int32_t hp,
                     _Float16* __restrict__ o_lat) {
   constexpr int LPH = 256 / HB;      // lanes per head in the weights phase
   constexpr int ELEMS = kMergeElems / CG, TPG = 256 / CG;   // elements per workgroup, threads per group
   __shared__ float wgt[kMaxChunks * HB];
   const int n_hb = hp / HB;
   const int row = blockIdx.y, vb = row / n_hb, hb = row - vb * n_hb, tid = threadIdx.x;
-  const int cg = tid / TPG, gt = tid % TPG;
+  const int cg = CG == 1 ? 0 : tid / TPG, gt = tid % TPG;
   const int b = vb / q_len, qi = vb - b * q_len;
-  const ChunkPlan plan = plan_chunks(seq_len, capacity, batch, slots, gran);
+  const ChunkPlan plan = plan_chunks(seq_len, capacity, cut);
   const int L = __builtin_amdgcn_readlane(plan.len, b) - (q_len - 1 - qi);
   const int first = b > 0 ? __builtin_amdgcn_readlane(plan.upto, b - 1) : 0;
-  const int nv = L > 0 ? min(min((L + plan.chunk - 1) / plan.chunk, n_launched - first), kMaxChunks) : 0;
-  const int64_t pb = (int64_t)(qi * n_hb + hb) * slots + first;
+  const int nv = L > 0 ? min(min(chunks_of(L, plan.chunk), n_launched - first), kMaxChunks) : 0;
+  const int64_t pb = (int64_t)(qi * n_hb + hb) * cut.stride + first;
   // element e8 (8 halves): latent quad x4 = e8 / (HB / 2), heads 2*(e8 % (HB / 2)) and +1;
   // the first batch of partial loads goes out before the weights are known
   const int64_t e0 = (int64_t)blockIdx.x * ELEMS + 8 * gt;
@@ -1146,15 +1153,39 @@ merge_latent_kernel(const _Float16* __restrict__ o_part, const float* __restrict
   }
   {
     const int h = tid / LPH, sub = tid % LPH;
+    // (loads in batches: one at a time, 126 chunks of one sequence took 13 us)
+    const float* mlh = ml_part + pb * 2 * HB + h;
     float m = -INFINITY;
-    for (int c = sub; c < nv; c += LPH) m = fmaxf(m, ml_part[(pb + c) * 2 * HB + h]);
+    for (int c0 = sub; c0 < nv; c0 += LPH * kMergeWBatch) {
+      float mc[kMergeWBatch];
+#pragma unroll
+      for (int k = 0; k < kMergeWBatch; ++k) {
+        const int c = c0 + LPH * k;
+        mc[k] = c < nv ? mlh[c * 2 * HB] : -INFINITY;
+      }
+#pragma unroll
+      for (int k = 0; k < kMergeWBatch; ++k) m = fmaxf(m, mc[k]);
+    }
 #pragma unroll
     for (int o = 1; o < LPH; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
     float tot = 0.f;
-    for (int c = sub; c < nv; c += LPH) {
-      const float wc = exp2f(ml_part[(pb + c) * 2 * HB + h] - m) * ml_part[(pb + c) * 2 * HB + HB + h];
-      wgt[c * HB + h] = wc;
-      tot += wc;
+    for (int c0 = sub; c0 < nv; c0 += LPH * kMergeWBatch) {
+      float mc[kMergeWBatch], lc[kMergeWBatch];
+#pragma unroll
+      for (int k = 0; k < kMergeWBatch; ++k) {
+        const int c = c0 + LPH * k;
+        mc[k] = c < nv ? mlh[c * 2 * HB] : 0.f;
+        lc[k] = c < nv ? mlh[c * 2 * HB + HB] : 0.f;
+      }
+#pragma unroll
+      for (int k = 0; k < kMergeWBatch; ++k) {
+        const int c = c0 + LPH * k;
+        if (c < nv) {
+          const float wc = exp2f(mc[k] - m) * lc[k];
+          wgt[c * HB + h] = wc;
+          tot += wc;
+        }
+      }
     }
 #pragma unroll
     for (int o = 1; o < LPH; o <<= 1) tot += __shfl_xor(tot, o, 64);
@@ -1373,7 +1404,8 @@ struct AbsorbPlan {
   int n_hb, hp;      // head blocks per row and padded heads per row (n_hb * hb)
   int rw, nw;        // 32-head kernel: latent columns per wave, waves
   int umax;          // 16-head kernel: 128-column units per wave (at most)
-  int n0, slots, gran;      // chunks per row on average, slots of one query and head block, chunk granularity
+  int n0;                   // chunks per row on average
+  ChunkCut cut;
   int n_launched;           // slots that can be in use at max_len
   size_t qt_bytes, opart_bytes, ml_bytes, olat_bytes;
 };
@@ -1411,11 +1443,25 @@ static AbsorbPlan plan_absorbed(const qsvd_layer& w, const qsvd_cache& c, int32_
   // blocks (one workgroup per CU): at most one round
   p.n0 = p.hb == kHeadBlk ? target_chunks((int)grows) : (int)(grows >= 256 ? 1 : 256 / grows);
   const int len = c.max_len > 0 ? c.max_len : 1;
-  // whole tiles (16-head plans: and ring rounds): half a tile costs a whole
-  // one's time and a partial more to merge
-  p.gran = p.hb == kHeadBlk ? 32 : 64;
-  p.slots = std::min(c.batch * p.n0, kMaxChunks);
-  p.n_launched = (int)std::min<int64_t>(p.slots, (int64_t)c.batch * ((len + p.gran - 1) / p.gran));
+  // 16-head plans: whole tiles and ring rounds.  32-head plans: the host's cut
+  // in half tiles (the chunk partials are rounded to fp16, and fewer of them
+  // average less of that out: whole tiles, one sequence of 65 rows, 4.03e-4
+  // -> 4.10e-4 over 200 inputs); the cut from all lengths in whole ones, since
+  // it spreads more chunks over the sequences than the host's does.
+  ChunkCut& k = p.cut;
+  const int even_gran = p.hb == kHeadBlk ? 16 : 64;
+  k.gran = p.hb == kHeadBlk ? 32 : 64;
+  k.batch = c.batch;
+  k.stride = c.batch * p.n0;
+  k.slots = std::min(k.stride, kMaxChunks);
+  k.even = ((len + p.n0 - 1) / p.n0 + even_gran - 1) / even_gran * even_gran;
+  k.n_even = (len + k.even - 1) / k.even;
+  k.even_lo = k.n_even > 1 ? k.even * (k.n_even - 1) : -1;
+  k.inv_mid = 1.f / (k.slots - c.batch / 2);
+  // (a little over: at the second step the fit is certain)
+  k.inv_step = 0.5f * (1.000001f / std::max(k.slots - c.batch, 1) - k.inv_mid);
+  p.n_launched = (int)std::max<int64_t>(
+      (int64_t)c.batch * k.n_even, std::min<int64_t>(k.slots, (int64_t)c.batch * ((len + k.gran - 1) / k.gran)));
   p.qt_bytes = (size_t)rows * p.hp * w.r * sizeof(_Float16);
   p.opart_bytes = (size_t)grows * p.n0 * w.r * p.hb * sizeof(_Float16);
   p.ml_bytes = (size_t)grows * p.n0 * 2 * p.hb * sizeof(float);
@@ -1451,8 +1497,8 @@ static hipError_t launch_latent(const AbsorbPlan& p, const qsvd_cache& c, int32_
   if (e != hipSuccess) return e;
   KernelScope ks("latent_attn", s);
   QSVD_LAUNCH(ks, kern, dim3(p.n_launched, q_len), dim3(NW * 64), lds, s, qt,
-                     (const uint8_t*)c.data, c.scale, c.seq_len, c.capacity, c.r, c.batch, p.slots,
-                     p.gran, q_len, pre, opart, ml);
+                     (const uint8_t*)c.data, c.scale, c.seq_len, c.capacity, c.r, p.cut,
+                     q_len, pre, opart, ml);
   return hipGetLastError();
 }
 
@@ -1465,8 +1511,7 @@ static hipError_t launch_latent_h16(const AbsorbPlan& p, const qsvd_cache& c, in
   if (e != hipSuccess) return e;
   KernelScope ks("latent_attn_h16", s);
   QSVD_LAUNCH(ks, kern, dim3(p.n_launched, q_len * p.n_hb), dim3(kH16Waves * 64), lds, s, qt,
-              (const uint8_t*)c.data, c.scale, c.seq_len, c.capacity, c.r, p.hp, c.batch, p.slots, p.gran, q_len,
-              opart, ml);
+              (const uint8_t*)c.data, c.scale, c.seq_len, c.capacity, c.r, p.hp, p.cut, q_len, opart, ml);
   return hipGetLastError();
 }
 
@@ -1552,22 +1597,23 @@ static hipError_t launch_merge_groups(const AttnArgs& a, const AbsorbPlan& p, in
   KernelScope ks("merge_latent", s);
   const dim3 grid((a.w->r * HB + kMergeElems / CG - 1) / (kMergeElems / CG), rows * p.n_hb);
   QSVD_LAUNCH(ks, (merge_latent_kernel<HB, CG>), grid, dim3(256), 0, s, opart, ml, c.seq_len, c.capacity,
-              c.batch, p.slots, p.gran, p.n_launched, a.q_len, a.w->r, p.hp, olat);
+              p.cut, p.n_launched, a.q_len, a.w->r, p.hp, olat);
   return hipGetLastError();
 }
 
-// Chunk groups per merge workgroup: eight (four) where one would leave a CU in
-// four (half the CUs) without a workgroup and the groups still have chunks to
-// share out.  One sequence of 1502 tokens, r = 1536: 22.8 us with one group
-// and 16-token chunks, 9.6 with eight and 32-token chunks.
+// Chunk groups per merge workgroup: eight (four) where one would leave three
+// CUs in four (half the CUs) without a workgroup and a thread's loads of all
+// its chunks are more than one batch.  One sequence of 1502 tokens, r = 1536
+// (94 chunks): 22.1 us with one group, 10.5 with eight; 32 sequences of 301
+// tokens, r = 128 (at most 8 chunks each): 4.1 with one, 5.4 with eight.
 template <int HB>
 static hipError_t launch_merge(const AttnArgs& a, const AbsorbPlan& p, int32_t rows, const _Float16* opart,
                                const float* ml, _Float16* olat, hipStream_t s) {
   const qsvd_cache& c = *a.c;
   const int64_t wgs = (int64_t)((a.w->r * HB + kMergeElems - 1) / kMergeElems) * rows * p.n_hb;
   const int per_seq = p.n_launched / c.batch;      // chunks of a sequence, on average at most
-  if (wgs <= 64 && per_seq >= 8) return launch_merge_groups<HB, 8>(a, p, rows, opart, ml, olat, s);
-  if (wgs <= 128 && per_seq >= 8) return launch_merge_groups<HB, 4>(a, p, rows, opart, ml, olat, s);
+  if (wgs <= 64 && per_seq >= kMergeBatch) return launch_merge_groups<HB, 8>(a, p, rows, opart, ml, olat, s);
+  if (wgs <= 128 && per_seq >= kMergeBatch) return launch_merge_groups<HB, 4>(a, p, rows, opart, ml, olat, s);
   return launch_merge_groups<HB, 1>(a, p, rows, opart, ml, olat, s);
 }
 

@@ -1395,6 +1395,43 @@ def test_decode_chunks_over_ragged_lengths(lengths, q_len, hq):
     _check_qlen_block(out.reshape(q.shape), ref, lengths, q_len)
 
 
+@pytest.mark.parametrize("lengths,cap_len,want", [
+    ([65], 65, 5),                      # half tiles of 16 rows
+    ([5000], 5000, 157),                # 256 slots: 32 rows each
+    ([300, 290, 300], 300, 57),         # 86 slots each: 16 rows, 19 chunks for every length
+    ([40, 3000], 3000, 96),             # 128 slots for the longest alone: 32 rows; from both lengths the same
+    ([100, 6400], 6400, 204),           # ... 64 rows; from both lengths 32
+], ids=["one65", "one5000", "even3", "skew3000", "skew6400"])
+def test_decode_chunk_partials(lengths, cap_len, want):
+    """How many partials the absorbed form makes (each is rounded to fp16, so
+    fewer of them would cost precision): those of the longest length cut for
+    the slots in half tiles, or of all lengths where they differ and that cuts
+    finer.  Counted in the caller's workspace, whose second part holds them."""
+    t = H.torch()
+    L = configs.LayerShape(d=256, n_q_heads=8, n_kv_heads=8, head_dim=64, r=128)
+    ol, dl = _random_factor_layer(L, 1508)
+    wl = configs.Workload(96, "partials", L, "gaussian", 8, 0, 8, O.CACHE_F16)
+    oc, dc = _prefilled_caches(wl, O.CACHE_F16, lengths, cap_len)
+    nb = len(lengths)
+    q = (np.random.default_rng(5).standard_normal((nb, 1, 8 * 64)) * 4.0).astype(np.float16)
+    q_dev, out = H.dev(q), H.empty((nb, 1, 8 * 64), t.float16)
+    size = B.qsvd_decode_workspace_size(dl.c, dc.c, 1, B.QSVD_ATTN_ABSORBED)
+    ws = t.full((size,), 0xFF, dtype=t.uint8, device="cuda")
+    H.say(f"chunk partials {lengths}")
+    B.check(B.qsvd_latent_decode_attention(dl.c, dc.c, B.ptr(q_dev), 1, B.QSVD_ATTN_ABSORBED, 0.0, B.ptr(out),
+                                           B.ptr(ws), size, B.stream_handle()))
+    part = 32 * L.r * 2                                  # 32 heads (padded) of r fp16 values
+    first = -(-nb * part // 256) * 256                   # after the absorbed queries
+    slots = nb * -(-256 // nb)
+    used = (H.host(ws)[first:first + slots * part].reshape(slots, part) != 0xFF).any(1)
+    assert int(used.sum()) == want
+    assert used[:want].all()
+    ref = O.attention_reference(ol, oc, q.astype(np.float64), q_len=1)
+    ok, info = H.close_enough(H.host(out), ref)
+    H.say(f"  max-abs, rel-L2, rms = {info}")
+    assert ok, info
+
+
 def test_decode_gqa_int4_cache_ragged(gqa):
     """Int4 latent cache (4-bit per-token codes of C with fp32 scales, two codes
     per byte): ragged prior lengths 3 / 50 / 97 of synthetic rows, then 3 decode

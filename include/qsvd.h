@@ -227,9 +227,7 @@ qsvd_status qsvd_prefill_attention(const void* q, const void* k, const void* v, 
  * (j, j + head_dim/2), j < head_dim/2, of every query and key head vector
  * turned by the angle i * rope_theta^(-2j/head_dim): the angle is formed in
  * revolutions and reduced to [0, 1) in fp64, its sine and cosine taken in
- * fp32 (for keys at every eighth 64-row tile, and advanced in fp32 by the
- * fixed angle of 64 positions between), and the turned rows rounded to fp16
- * before the products.  Values are
+ * fp32, and the turned rows rounded to fp16 before the products.  Values are
  * not turned.  A decode step that continues the sequence over its cache sees
  * the same key positions.  Same arguments, requirements and errors as
  * qsvd_prefill_attention; rope_theta must be finite and > 1

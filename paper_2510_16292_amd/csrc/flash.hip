@@ -37,28 +37,18 @@
 //
 // Rotary layers (ROPE): a query row is turned once, in registers, at its
 // position within the sequence; a key row is turned while its tile moves from
-// registers into LDS, at its own position (rotate-half pairs j, j + dh/2 by
-// the angle pos * theta^(-2j/dh)).  The angle is formed in revolutions in
-// fp64 and reduced to [0, 1) there, then sine and cosine come from the
-// hardware's revolution-based instructions in fp32; the turned rows are
-// rounded to fp16 for the matrix cores, like the unturned ones.  A thread
-// turns the same channels of every 64th key, so between the exact angles of
-// every eighth tile it advances (cos, sin) by the fixed angle of 64 positions
-// (four fp32 operations; an fp64 angle with its sine and cosine costs about
-// twenty).
+// registers into LDS, at its own position (flash.h says how).
 #include <math.h>
 
 #include <algorithm>
 
 #include "common.h"
+#include "flash.h"
 #include "launch.h"
 
 namespace qsvd {
 
-constexpr int kFaK = 64;        // keys per tile
 constexpr int kFaQW = 32;       // queries per wave
-constexpr int kFaResync = 8;    // tiles between exact key angles
-constexpr float kFaLog2e = 1.4426950408889634f;
 
 template <int DH, int NW, int KSP>
 struct FaCfg {
@@ -70,8 +60,7 @@ struct FaCfg {
   static constexpr int kOut = UW * kFaQW * OST * 2;
   static constexpr int kJoin = KSP > 1 ? UW * (64 * 4 * (DH / 2) + 64 * 8) : 0;   // a share's fp32 rows and (m, l)
   static constexpr size_t kLds = std::max({2 * KSP * kBuf, kOut, kJoin});
-  // + revolutions per position of each pair, then (cos, sin) of its 64-position step
-  static constexpr size_t kLdsRope = kLds + (size_t)(DH / 2) * (sizeof(double) + sizeof(float2));
+  static constexpr size_t kLdsRope = kLds + (size_t)(DH / 2) * sizeof(double);   // + revolutions per position of each pair
   static constexpr int kLPW = kTile / 1024 / UW;              // direct loads per wave and tile of one operand
   static_assert(kTile % (1024 * UW) == 0 && (KSP == 1 || KSP == 2), "whole 1 KB loads per wave");
 };
@@ -102,47 +91,6 @@ __device__ __forceinline__ int fa_vslot(int row, int c) {
 __device__ __forceinline__ void fa_direct_load(const _Float16* base, uint32_t off, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
                : "memory", "m0");
-}
-
-// Both lanes of a pair (l, l ^ 32) get the max / sum of their two values:
-// v_permlane32_swap with both registers holding the value gives each lane its
-// partner's (issued as asm with both registers read-write; the s_nop covers
-// the hazard of a vector write just before).
-__device__ __forceinline__ void fa_swap32(uint32_t& a, uint32_t& b) {
-  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-}
-__device__ __forceinline__ float fa_pair_max(float x) {
-  uint32_t a = __builtin_bit_cast(uint32_t, x), b = a;
-  fa_swap32(a, b);
-  return fmaxf(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
-}
-__device__ __forceinline__ float fa_pair_sum(float x) {
-  uint32_t a = __builtin_bit_cast(uint32_t, x), b = a;
-  fa_swap32(a, b);
-  return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
-}
-
-// Turn the rotate-half pairs (a[e], b[e]) of channels j0 + e by the angle
-// pos * theta^(-2j/dh): freq[j] holds theta^(-2j/dh) / (2 pi), so the angle
-// in revolutions is formed and reduced to [0, 1) in fp64 before the fp32
-// sine and cosine.
-__device__ __forceinline__ void fa_angle(int pos, double freq, float* c, float* s) {
-  double rev = (double)pos * freq;
-  rev -= floor(rev);
-  const float x = (float)rev;
-  *c = __builtin_amdgcn_cosf(x);
-  *s = __builtin_amdgcn_sinf(x);
-}
-__device__ __forceinline__ void fa_turn8(f16x8& a, f16x8& b, const float* c, const float* s) {
-  f16x8 ra, rb;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const float fa = (float)a[e], fb = (float)b[e];
-    ra[e] = (_Float16)fmaf(fa, c[e], -(fb * s[e]));
-    rb[e] = (_Float16)fmaf(fb, c[e], fa * s[e]);
-  }
-  a = ra;
-  b = rb;
 }
 
 // Cache mode: the queries are the last q_len positions of each sequence of a
@@ -219,19 +167,8 @@ prefill_flash_kernel(const _Float16* __restrict__ q, const _Float16* __restrict_
   const int wave_last = live ? min(q_off + qw0 + kFaQW - 1, q_off + nq - 1) : -1;
 
   double* freq = reinterpret_cast<double*>(fa_smem + C::kLds);
-  float2* step = reinterpret_cast<float2*>(freq + DH / 2);
   if (MODE != FA_PLAIN) {
-    if (tid < DH / 2) {
-      const double f = exp2(-2.0 * tid / DH * log2_theta);
-      freq[tid] = f * 0.15915494309189533576888376337251;
-      if (ROPE && n_tiles > 1) {
-        double rev = (double)kFaK * freq[tid];
-        rev -= floor(rev);
-        float sn, cs;
-        sincosf((float)(rev * 6.283185307179586476925286766559), &sn, &cs);
-        step[tid] = make_float2(cs, sn);
-      }
-    }
+    if (tid < DH / 2) freq[tid] = fa_freq(tid, DH, log2_theta);
     __syncthreads();
   }
 
@@ -244,12 +181,7 @@ prefill_flash_kernel(const _Float16* __restrict__ q, const _Float16* __restrict_
     for (int s = 0; s < KS; ++s) qf[s] = *reinterpret_cast<const f16x8*>(qrow + 16 * s);
     if (MODE != FA_PLAIN) {                         // slot s pairs with slot s + KS/2 (channels dh/2 further)
 #pragma unroll
-      for (int s = 0; s < KS / 2; ++s) {
-        float cs[8], sn[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) fa_angle(q_off + qi, freq[16 * s + 8 * hl + e], &cs[e], &sn[e]);
-        fa_turn8(qf[s], qf[s + KS / 2], cs, sn);
-      }
+      for (int s = 0; s < KS / 2; ++s) fa_rope8(qf[s], qf[s + KS / 2], q_off + qi, freq + 16 * s + 8 * hl);
     }
   }
 
@@ -290,7 +222,6 @@ prefill_flash_kernel(const _Float16* __restrict__ q, const _Float16* __restrict_
   static_assert(!ROPE || kFaK * PR <= NW * 64, "one pair run per thread");
   const int krow = tid / PR, kpc = tid % PR;
   i32x4 kr[2];
-  float kc[8], ksn[8];
   auto load_keys = [&](int t) {
     if (kAllTurn || krow < kFaK) {
       const int key = min(t * kFaK + krow, nk - 1);
@@ -301,20 +232,8 @@ prefill_flash_kernel(const _Float16* __restrict__ q, const _Float16* __restrict_
   };
   auto store_keys = [&](int t, uint8_t* base) {
     if (kAllTurn || krow < kFaK) {
-      if (t % kFaResync == 0) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) fa_angle(t * kFaK + krow, freq[8 * kpc + e], &kc[e], &ksn[e]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float2 d = step[8 * kpc + e];
-          const float c0 = kc[e];
-          kc[e] = fmaf(c0, d.x, -(ksn[e] * d.y));
-          ksn[e] = fmaf(ksn[e], d.x, c0 * d.y);
-        }
-      }
       f16x8 a = __builtin_bit_cast(f16x8, kr[0]), bb = __builtin_bit_cast(f16x8, kr[1]);
-      fa_turn8(a, bb, kc, ksn);
+      fa_rope8(a, bb, t * kFaK + krow, freq + 8 * kpc);
       _Float16* ks = reinterpret_cast<_Float16*>(base);
       *reinterpret_cast<f16x8*>(ks + 8 * fa_kslot<DH>(krow, kpc)) = a;
       *reinterpret_cast<f16x8*>(ks + 8 * fa_kslot<DH>(krow, kpc + PR)) = bb;
@@ -575,8 +494,7 @@ rope_keys_kernel(_Float16* __restrict__ kv, const int32_t* __restrict__ seq_len,
   if (t >= min(seq_len[b], capacity)) return;
   float c[8], sn[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e)
-    fa_angle(t, exp2(-2.0 * (8 * pc + e) / DH * log2_theta) * 0.15915494309189533576888376337251, &c[e], &sn[e]);
+  for (int e = 0; e < 8; ++e) fa_angle(t, fa_freq(8 * pc + e, DH, log2_theta), &c[e], &sn[e]);
   _Float16* row = kv + ((int64_t)b * capacity + t) * ldkv + 8 * pc;
   for (int g = 0; g < Hkv; ++g, row += DH) {
     f16x8 x = *reinterpret_cast<const f16x8*>(row), y = *reinterpret_cast<const f16x8*>(row + DH / 2);

@@ -23,71 +23,40 @@
 //
 // Rotary layers (ROPE): a query row is turned once, in registers, at its
 // position within the sequence; a key row is turned while its tile moves from
-// registers into LDS, at its own position (rotate-half pairs j, j + dh/2 by
-// the angle pos * theta^(-2j/dh)).  The angle is formed in revolutions in
-// fp64 and reduced to [0, 1) there, then sine and cosine come from the
-// hardware's revolution-based instructions in fp32; the turned rows are
-// rounded to fp16 for the matrix cores, like the unturned ones.
+// registers into LDS, at its own position (flash.h says how).
 #include <math.h>
 
 #include "common.h"
+#include "flash.h"
 #include "launch.h"
 
 namespace qsvd {
 
 constexpr int kFsQ = 128;       // queries per workgroup
-constexpr int kFsK = 64;        // keys per tile
 constexpr int kFsWaves = 8;
-constexpr int kFsQW = kFsQ / kFsWaves;   // queries per wave
-constexpr int kFsQB = kFsQW / 16;        // 16-query blocks per wave
-constexpr float kFsLog2e = 1.4426950408889634f;
+constexpr int kFsQW = kFsQ / kFsWaves;   // queries per wave: one block of 16
+static_assert(kFsQW == 16);
 
 template <int DH>
 struct FsCfg {
   static constexpr int KST = DH + 8;       // K tile row stride (halves): 16-byte row reads hit every bank once
   static constexpr int VST = DH + 16;      // V tile row stride: the transposing reads hit distinct banks
   static constexpr int OST = DH + 8;       // output staging row stride
-  static constexpr size_t kK = (size_t)kFsK * KST * 2, kV = (size_t)kFsK * VST * 2;
+  static constexpr size_t kK = (size_t)kFaK * KST * 2, kV = (size_t)kFaK * VST * 2;
   static constexpr size_t kOut = (size_t)kFsWaves * kFsQW * OST * 2;
   static constexpr size_t kLds = kK + kV > kOut ? kK + kV : kOut;
   static constexpr size_t kLdsRope = kLds + (size_t)(DH / 2) * sizeof(double);   // + revolutions per position of each pair
-  static constexpr int kChunks = kFsK * DH / 8;               // 16-byte runs per K (or V) tile
+  static constexpr int kChunks = kFaK * DH / 8;               // 16-byte runs per K (or V) tile
   static constexpr int kPerThread = kChunks / (kFsWaves * 64);
   static_assert(kChunks % (kFsWaves * 64) == 0, "whole runs per thread");
 };
-
-// Max and sum over the four 16-lane rows of a wave (lanes l, l ^ 16, l ^ 32,
-// l ^ 48), every lane receiving the result: gfx950's v_permlane32_swap and
-// v_permlane16_swap with both registers holding the value give each lane its
-// partner's value at vector-ALU latency (issued as asm with both registers
-// read-write; the s_nop covers the hazard of a vector write just before).
-__device__ __forceinline__ void fs_swap32(uint32_t& a, uint32_t& b) {
-  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-}
-__device__ __forceinline__ void fs_swap16(uint32_t& a, uint32_t& b) {
-  asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-}
-__device__ __forceinline__ float fs_rows4_max(float x) {
-  uint32_t a = __builtin_bit_cast(uint32_t, x), b = a;
-  fs_swap32(a, b);
-  uint32_t c = __builtin_bit_cast(uint32_t, fmaxf(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b))), e = c;
-  fs_swap16(c, e);
-  return fmaxf(__builtin_bit_cast(float, c), __builtin_bit_cast(float, e));
-}
-__device__ __forceinline__ float fs_rows4_sum(float x) {
-  uint32_t a = __builtin_bit_cast(uint32_t, x), b = a;
-  fs_swap32(a, b);
-  uint32_t c = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b)), e = c;
-  fs_swap16(c, e);
-  return __builtin_bit_cast(float, c) + __builtin_bit_cast(float, e);
-}
 
 // Rotary staging of a key tile: thread tid turns the 8 pairs of run pc
 // (channels 8 pc .. +7 with their partners dh/2 further) of row tid / PR.
 template <int DH>
 struct FsRope {
   static constexpr int PR = DH / 16;                     // pair runs per row
-  static constexpr int kActive = kFsK * PR;              // threads with a key row to turn
+  static constexpr int kActive = kFaK * PR;              // threads with a key row to turn
   static_assert(kActive <= kFsWaves * 64, "one pair run per thread");
   static constexpr int KR = FsCfg<DH>::kPerThread > 2 ? FsCfg<DH>::kPerThread : 2;   // key registers per thread
 };
@@ -103,7 +72,7 @@ __device__ __forceinline__ void fs_load_tile(const _Float16* __restrict__ k, con
 #pragma unroll
   for (int i = 0; i < FsCfg<DH>::kPerThread; ++i) {
     const int e = tid + kFsWaves * 64 * i, row = e / RUNS, c8 = e - row * RUNS;
-    const int key = min(t * kFsK + row, n - 1);
+    const int key = min(t * kFaK + row, n - 1);
     const int64_t off = (int64_t)(tok0 + key) * ldkv + g * DH + 8 * c8;
     if (!ROPE) kr[i] = *reinterpret_cast<const i32x4*>(k + off);
     vr[i] = *reinterpret_cast<const i32x4*>(v + off);
@@ -111,31 +80,11 @@ __device__ __forceinline__ void fs_load_tile(const _Float16* __restrict__ k, con
   if (ROPE && tid < FsRope<DH>::kActive) {
     constexpr int PR = FsRope<DH>::PR;
     const int row = tid / PR, pc = tid - row * PR;
-    const int key = min(t * kFsK + row, n - 1);
+    const int key = min(t * kFaK + row, n - 1);
     const _Float16* src = k + (int64_t)(tok0 + key) * ldkv + g * DH + 8 * pc;
     kr[0] = *reinterpret_cast<const i32x4*>(src);
     kr[1] = *reinterpret_cast<const i32x4*>(src + DH / 2);
   }
-}
-
-// Turn the rotate-half pairs (a[e], b[e]) of channels j0 + e by the angle
-// pos * theta^(-2j/dh): freq[j] holds theta^(-2j/dh) / (2 pi), so the angle
-// in revolutions is formed and reduced to [0, 1) in fp64 before the fp32
-// sine and cosine.
-__device__ __forceinline__ void fs_rope8(f16x8& a, f16x8& b, int pos, const double* freq) {
-  f16x8 ra, rb;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    double rev = (double)pos * freq[e];
-    rev -= floor(rev);
-    const float x = (float)rev;
-    const float c = __builtin_amdgcn_cosf(x), sn = __builtin_amdgcn_sinf(x);
-    const float fa = (float)a[e], fb = (float)b[e];
-    ra[e] = (_Float16)(fa * c - fb * sn);
-    rb[e] = (_Float16)(fb * c + fa * sn);
-  }
-  a = ra;
-  b = rb;
 }
 
 // ... and its copy into the LDS tiles (turning the keys of a rotary layer at
@@ -155,7 +104,7 @@ __device__ __forceinline__ void fs_store_tile(_Float16* ks, _Float16* vs, int ti
     constexpr int PR = FsRope<DH>::PR;
     const int row = tid / PR, pc = tid - row * PR;
     f16x8 a = __builtin_bit_cast(f16x8, kr[0]), b = __builtin_bit_cast(f16x8, kr[1]);
-    fs_rope8(a, b, t * kFsK + row, freq + 8 * pc);
+    fa_rope8(a, b, t * kFaK + row, freq + 8 * pc);
     *reinterpret_cast<f16x8*>(ks + row * FsCfg<DH>::KST + 8 * pc) = a;
     *reinterpret_cast<f16x8*>(ks + row * FsCfg<DH>::KST + 8 * pc + DH / 2) = b;
   }
@@ -164,9 +113,8 @@ __device__ __forceinline__ void fs_store_tile(_Float16* ks, _Float16* vs, int ti
 template <int DH, bool ROPE>
 __global__ void __launch_bounds__(kFsWaves * 64, 2)
 prefill_flash_short_kernel(const _Float16* __restrict__ q, const _Float16* __restrict__ k, const _Float16* __restrict__ v,
-                     const int32_t* __restrict__ cu, int32_t n_seq, int32_t Hq, int32_t Hkv, int32_t n_qt,
-                     float scale_log2, double log2_theta, int32_t max_seqlen,
-                           _Float16* __restrict__ out) {
+                           const int32_t* __restrict__ cu, int32_t n_seq, int32_t Hq, int32_t Hkv, int32_t n_qt,
+                           float scale_log2, double log2_theta, int32_t max_seqlen, _Float16* __restrict__ out) {
   using C = FsCfg<DH>;
   constexpr int KS = DH / 32;      // contraction steps of the score product
   constexpr int OB = DH / 16;      // 16-channel blocks of the output
@@ -192,42 +140,31 @@ prefill_flash_short_kernel(const _Float16* __restrict__ q, const _Float16* __res
   if (q0 >= n) return;
   double* freq = reinterpret_cast<double*>(fs_smem + C::kLds);
   if (ROPE) {
-    if (tid < DH / 2) freq[tid] = exp2(-2.0 * tid / DH * log2_theta) * 0.15915494309189533576888376337251;
+    if (tid < DH / 2) freq[tid] = fa_freq(tid, DH, log2_theta);
     __syncthreads();
   }
   const int g_kv = (h * Hkv) / Hq;
   const int ldq = Hq * DH, ldkv = Hkv * DH;
   const int kend = min(n, q0 + kFsQ);               // keys this tile of queries can see
-  const int n_tiles = (kend + kFsK - 1) / kFsK;
+  const int n_tiles = (kend + kFaK - 1) / kFaK;
   const int qw0 = q0 + kFsQW * w;                   // this wave's first query
-  int my_q[kFsQB];                                  // this lane's query in each block
-#pragma unroll
-  for (int qb = 0; qb < kFsQB; ++qb) my_q[qb] = qw0 + 16 * qb + l16;
+  const int my_q = qw0 + l16;                       // this lane's query
 
   // query slots of the score product: step s, lane group g -> channels 32 s + 8 g .. +7
-  f16x8 qf[kFsQB][KS];
+  f16x8 qf[KS];
+  const _Float16* qrow = q + (int64_t)(row0 + min(my_q, n - 1)) * ldq + h * DH + 8 * g;
 #pragma unroll
-  for (int qb = 0; qb < kFsQB; ++qb) {
-    const _Float16* qrow = q + (int64_t)(row0 + min(my_q[qb], n - 1)) * ldq + h * DH + 8 * g;
+  for (int s = 0; s < KS; ++s) qf[s] = *reinterpret_cast<const f16x8*>(qrow + 32 * s);
+  if (ROPE) {                                       // slot s pairs with slot s + KS/2 (channels dh/2 further)
 #pragma unroll
-    for (int s = 0; s < KS; ++s) qf[qb][s] = *reinterpret_cast<const f16x8*>(qrow + 32 * s);
-    if (ROPE) {                                     // slot s pairs with slot s + KS/2 (channels dh/2 further)
-#pragma unroll
-      for (int s = 0; s < KS / 2; ++s)
-        fs_rope8(qf[qb][s], qf[qb][s + KS / 2], min(my_q[qb], n - 1), freq + 32 * s + 8 * g);
-    }
+    for (int s = 0; s < KS / 2; ++s) fa_rope8(qf[s], qf[s + KS / 2], min(my_q, n - 1), freq + 32 * s + 8 * g);
   }
 
   i32x4 kr[FsRope<DH>::KR], vr[C::kPerThread];
-  f32x4 o[kFsQB][OB];
-  float m_run[kFsQB], l_run[kFsQB];
+  f32x4 o[OB];
 #pragma unroll
-  for (int qb = 0; qb < kFsQB; ++qb) {
-#pragma unroll
-    for (int ob = 0; ob < OB; ++ob) o[qb][ob] = f32x4{};
-    m_run[qb] = -INFINITY;
-    l_run[qb] = 0.f;
-  }
+  for (int ob = 0; ob < OB; ++ob) o[ob] = f32x4{};
+  float m_run = -INFINITY, l_run = 0.f;
   typedef short s16x4 __attribute__((ext_vector_type(4)));
   typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
@@ -237,71 +174,64 @@ prefill_flash_short_kernel(const _Float16* __restrict__ q, const _Float16* __res
     fs_store_tile<DH, ROPE>(ks, vs, tid, t, freq, kr, vr);
     __syncthreads();
     if (t + 1 < n_tiles) fs_load_tile<DH, ROPE>(k, v, row0, n, ldkv, g_kv, t + 1, tid, kr, vr);
-    const int kt0 = t * kFsK;
-    if (kt0 > qw0 + kFsQW - 1) continue;    // every key of the tile is after this wave's queries
-    // S^T: key block kb, lane (query l16 of block qb, group g) holds keys kt0 + 16 kb + 4 g + v
-    f32x4 sacc[kFsQB][4];
+    const int kt0 = t * kFaK;
+    if (kt0 > qw0 + kFsQW - 1) continue;            // every key of the tile is after this wave's queries
+    // S^T: key block kb, lane (query l16, group g) holds keys kt0 + 16 kb + 4 g + v
+    f32x4 sacc[4];
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) {
-#pragma unroll
-      for (int qb = 0; qb < kFsQB; ++qb) sacc[qb][kb] = f32x4{};
+      sacc[kb] = f32x4{};
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
         const f16x8 kf = *reinterpret_cast<const f16x8*>(ks + (16 * kb + l16) * C::KST + 32 * s + 8 * g);
-#pragma unroll
-        for (int qb = 0; qb < kFsQB; ++qb)
-          sacc[qb][kb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qf[qb][s], sacc[qb][kb], 0, 0, 0);
+        sacc[kb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qf[s], sacc[kb], 0, 0, 0);
       }
     }
-    // softmax per query block; the scores become the probabilities in place
-    // (tiles wholly before this wave's first query and inside the sequence
-    // need no mask)
-    const bool full = kt0 + kFsK - 1 <= qw0 && kt0 + kFsK <= n;
-    float p[kFsQB][4][4];
+    // softmax (tiles wholly before this wave's first query and inside the
+    // sequence need no mask)
+    const bool full = kt0 + kFaK - 1 <= qw0 && kt0 + kFaK <= n;
+    float p[4][4];
+    float mx = -INFINITY;
+    if (full) {
 #pragma unroll
-    for (int qb = 0; qb < kFsQB; ++qb) {
-      float mx = -INFINITY;
-      if (full) {
+      for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
+        for (int vv = 0; vv < 4; ++vv) {
+          p[kb][vv] = sacc[kb][vv] * scale_log2;
+          mx = fmaxf(mx, p[kb][vv]);
+        }
+    } else {
 #pragma unroll
-          for (int vv = 0; vv < 4; ++vv) {
-            p[qb][kb][vv] = sacc[qb][kb][vv] * scale_log2;
-            mx = fmaxf(mx, p[qb][kb][vv]);
-          }
-      } else {
+      for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
+        for (int vv = 0; vv < 4; ++vv) {
+          const int key = kt0 + 16 * kb + 4 * g + vv;
+          p[kb][vv] = (key <= my_q && key < n) ? sacc[kb][vv] * scale_log2 : -INFINITY;
+          mx = fmaxf(mx, p[kb][vv]);
+        }
+    }
+    const float m_new = fmaxf(m_run, fa_rows4_max(mx));
+    float alpha = 1.f, ps = 0.f;
+    if (m_new == -INFINITY) {
 #pragma unroll
-          for (int vv = 0; vv < 4; ++vv) {
-            const int key = kt0 + 16 * kb + 4 * g + vv;
-            p[qb][kb][vv] = (key <= my_q[qb] && key < n) ? sacc[qb][kb][vv] * scale_log2 : -INFINITY;
-            mx = fmaxf(mx, p[qb][kb][vv]);
-          }
-      }
-      const float m_new = fmaxf(m_run[qb], fs_rows4_max(mx));
-      float alpha = 1.f, ps = 0.f;
-      if (m_new == -INFINITY) {
+      for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
+        for (int vv = 0; vv < 4; ++vv) p[kb][vv] = 0.f;
+    } else {
+      alpha = __builtin_amdgcn_exp2f(m_run - m_new);
 #pragma unroll
-          for (int vv = 0; vv < 4; ++vv) p[qb][kb][vv] = 0.f;
-      } else {
-        alpha = __builtin_amdgcn_exp2f(m_run[qb] - m_new);
+      for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
+        for (int vv = 0; vv < 4; ++vv) {
+          p[kb][vv] = __builtin_amdgcn_exp2f(p[kb][vv] - m_new);
+          ps += p[kb][vv];
+        }
+    }
+    l_run = l_run * alpha + fa_rows4_sum(ps);
+    m_run = m_new;
+    if (__any(alpha != 1.f)) {
 #pragma unroll
-          for (int vv = 0; vv < 4; ++vv) {
-            p[qb][kb][vv] = __builtin_amdgcn_exp2f(p[qb][kb][vv] - m_new);
-            ps += p[qb][kb][vv];
-          }
-      }
-      l_run[qb] = l_run[qb] * alpha + fs_rows4_sum(ps);
-      m_run[qb] = m_new;
-      if (__any(alpha != 1.f)) {
-#pragma unroll
-        for (int ob = 0; ob < OB; ++ob) o[qb][ob] *= alpha;
-      }
+      for (int ob = 0; ob < OB; ++ob) o[ob] *= alpha;
     }
     // O^T += V^T P^T in two 32-key steps st: k-slot e of lane group g is key
     // 32 st + 16 (e / 4) + 4 g + e % 4, i.e. score p[2 st + e / 4][e % 4].
@@ -311,11 +241,9 @@ prefill_flash_short_kernel(const _Float16* __restrict__ q, const _Float16* __res
     // 8 + i/4, 12 + i/4: channel 16 ob + i at keys 4g .. 4g+3 of the block.
 #pragma unroll
     for (int st = 0; st < 2; ++st) {
-      f16x8 pf[kFsQB];
+      f16x8 pf;
 #pragma unroll
-      for (int qb = 0; qb < kFsQB; ++qb)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) pf[qb][e] = (_Float16)p[qb][2 * st + (e >> 2)][e & 3];
+      for (int e = 0; e < 8; ++e) pf[e] = (_Float16)p[2 * st + (e >> 2)][e & 3];
       const int key = 32 * st + 4 * g + (l16 >> 2);
 #pragma unroll
       for (int ob = 0; ob < OB; ++ob) {
@@ -324,25 +252,21 @@ prefill_flash_short_kernel(const _Float16* __restrict__ q, const _Float16* __res
         const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(a0 + 16 * C::VST));
         const f16x4 flo = __builtin_bit_cast(f16x4, lo), fhi = __builtin_bit_cast(f16x4, hi);
         const f16x8 a = {flo[0], flo[1], flo[2], flo[3], fhi[0], fhi[1], fhi[2], fhi[3]};
-#pragma unroll
-        for (int qb = 0; qb < kFsQB; ++qb) o[qb][ob] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, pf[qb], o[qb][ob], 0, 0, 0);
+        o[ob] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, pf, o[ob], 0, 0, 0);
       }
     }
   }
 
   // O / l through LDS, so that each query row leaves as 16-byte runs: lane
-  // (l16, g) holds query qw0 + 16 qb + l16 at channels 16 ob + 4 g .. +3.
+  // (l16, g) holds query qw0 + l16 at channels 16 ob + 4 g .. +3.
   __syncthreads();
   _Float16* ost = reinterpret_cast<_Float16*>(fs_smem) + w * kFsQW * C::OST;
+  const float inv_l = l_run > 0.f ? 1.f / l_run : 0.f;
 #pragma unroll
-  for (int qb = 0; qb < kFsQB; ++qb) {
-    const float inv_l = l_run[qb] > 0.f ? 1.f / l_run[qb] : 0.f;
-#pragma unroll
-    for (int ob = 0; ob < OB; ++ob) {
-      const f16x4 v4 = {(_Float16)(o[qb][ob][0] * inv_l), (_Float16)(o[qb][ob][1] * inv_l),
-                        (_Float16)(o[qb][ob][2] * inv_l), (_Float16)(o[qb][ob][3] * inv_l)};
-      *reinterpret_cast<f16x4*>(ost + (16 * qb + l16) * C::OST + 16 * ob + 4 * g) = v4;
-    }
+  for (int ob = 0; ob < OB; ++ob) {
+    const f16x4 v4 = {(_Float16)(o[ob][0] * inv_l), (_Float16)(o[ob][1] * inv_l), (_Float16)(o[ob][2] * inv_l),
+                      (_Float16)(o[ob][3] * inv_l)};
+    *reinterpret_cast<f16x4*>(ost + l16 * C::OST + 16 * ob + 4 * g) = v4;
   }
   __syncthreads();
 #pragma unroll
@@ -365,7 +289,7 @@ static hipError_t launch_short(const PrefillAttnArgs& a, hipStream_t s) {
   const int n_qt = (a.max_seqlen + kFsQ - 1) / kFsQ;
   KernelScope ks(ROPE ? "prefill_flash_rope" : "prefill_flash", s);
   QSVD_LAUNCH(ks, kern, dim3((unsigned)(a.batch * a.n_q_heads * n_qt)), dim3(kFsWaves * 64), lds, s, a.q, a.k, a.v,
-              a.cu_seqlens, a.batch, a.n_q_heads, a.n_kv_heads, n_qt, a.sm_scale * kFsLog2e,
+              a.cu_seqlens, a.batch, a.n_q_heads, a.n_kv_heads, n_qt, a.sm_scale * kFaLog2e,
               ROPE ? log2((double)a.rope_theta) : 0.0, a.max_seqlen, a.out);
   return hipGetLastError();
 }

@@ -690,6 +690,54 @@ def test_prefill_attention_past_max_seqlen(theta):
     assert np.all(got[most:] == 7.0)
 
 
+def test_prefill_attention_rope_turns_keys_alike():
+    """Every launch form turns a key at a position into the same fp16 row.  Each
+    head's queries and keys have one pair of channels (another per sequence and
+    head) and unit length, so a score is a sum of two exact products, and the
+    scale makes an fp16 step of a key element (about 1e-3 of a score of 1) two
+    thirds of a nat while fp32 rounding of the scores stays below
+    2000 * 2^-22 = 5e-4: a row that another form had turned otherwise would
+    move the output by far more than the tolerance, which allows those and the
+    fp16 roundings of probabilities and outputs (2^-10 of values up to 4.5)."""
+    hq, dh, n, seqs, theta = 2, 128, 512, 32, 1e4
+    g = np.random.default_rng(77)
+    v = H.dev(g.standard_normal((seqs * n, hq * dh)).astype(np.float16))
+
+    def unit_pairs():
+        x = np.zeros((seqs, n, hq, dh), np.float16)
+        ang = g.uniform(0.0, 2.0 * np.pi, (seqs, n, hq))
+        for b in range(seqs):
+            for h in range(hq):
+                j = b * hq + h
+                x[b, :, h, j], x[b, :, h, j + 64] = np.cos(ang[b, :, h]), np.sin(ang[b, :, h])
+        return H.dev(x.reshape(seqs * n, hq * dh))
+
+    for rep in range(4):
+        q, k = unit_pairs(), unit_pairs()
+
+        def run(first, count, most):
+            rows = slice(first * n, (first + count) * n)
+            out = H.prefill_attention(q[rows].contiguous(), k[rows].contiguous(), v[rows].contiguous(), [n] * count, hq,
+                                      hq, dh, max_seqlen=most, sm_scale=2000.0, rope_theta=theta)
+            return H.host(out).astype(np.float64)
+
+        H.say(f"rope keys alike {rep}")
+        # at most one workgroup per CU: two key shares; with larger bounds of the
+        # lengths four units, eight units; 384 rows: the short-prompt kernel
+        shares = np.concatenate([run(b, 4, n) for b in range(0, seqs, 4)])
+        for most, name in ((n, "together"), (900, "four units"), (4000, "eight units")):
+            err = np.abs(run(0, seqs, most) - shares).max()
+            assert err < 1e-2, (name, err)
+        cut = 384
+        rows = (np.arange(seqs * n) % n < cut)
+        short = np.concatenate([H.host(H.prefill_attention(q[b * n:b * n + cut].contiguous(),
+                                                           k[b * n:b * n + cut].contiguous(),
+                                                           v[b * n:b * n + cut].contiguous(), [cut], hq, hq, dh,
+                                                           sm_scale=2000.0, rope_theta=theta)) for b in range(seqs)])
+        err = np.abs(short.astype(np.float64) - shares[rows]).max()
+        assert err < 1e-2, ("short", err)
+
+
 def test_prefill_attention_rope_llava7b_full():
     """The LLaVA-1.5-7B-shaped prompt batch at full size (4 x 640 tokens,
     32 heads x 128, rotary base 10000) in the bench's launch configuration,

@@ -108,7 +108,6 @@ prefill_flash_kernel(const _Float16* __restrict__ q, const _Float16* __restrict_
                      float scale_log2, double log2_theta, FaCacheArgs ca, _Float16* __restrict__ out) {
   using C = FaCfg<DH, NW, KSP>;
   constexpr bool ROPE = MODE == FA_ROPE;
-  static_assert(!ROPE || KSP == 1, "turned keys are shared by the whole workgroup");
   constexpr int UW = C::UW;
   constexpr int KS = DH / 16;      // contraction steps of the score product
   constexpr int OB = DH / 32;      // 32-channel blocks of the output
@@ -215,29 +214,33 @@ prefill_flash_kernel(const _Float16* __restrict__ q, const _Float16* __restrict_
       }
     }
   };
-  // Rotary keys: thread tid turns the 8 pairs of run pc (channels 8 pc .. +7
-  // with their partners dh/2 further) of row tid / PR.
-  constexpr int PR = DH / 16;
-  constexpr bool kAllTurn = !ROPE || kFaK * PR == NW * 64;
-  static_assert(!ROPE || kFaK * PR <= NW * 64, "one pair run per thread");
-  const int krow = tid / PR, kpc = tid % PR;
-  i32x4 kr[2];
+  // Rotary keys: thread st of a share turns, in key rows st / PR + kRows i, the
+  // 8 pairs of run pc (channels 8 pc .. +7 with their partners dh/2 further).
+  constexpr int PR = DH / 16, kRows = 64 * UW / PR, kTurns = (kFaK + kRows - 1) / kRows;
+  constexpr bool kAllTurn = !ROPE || kRows * kTurns == kFaK;
+  const int krow = (wu * 64 + lane) / PR, kpc = lane % PR;
+  i32x4 kr[kTurns][2];
   auto load_keys = [&](int t) {
-    if (kAllTurn || krow < kFaK) {
-      const int key = min(t * kFaK + krow, nk - 1);
-      const _Float16* src = k + (int64_t)(k_row0 + key) * ldkv + g_kv * DH + 8 * kpc;
-      kr[0] = *reinterpret_cast<const i32x4*>(src);
-      kr[1] = *reinterpret_cast<const i32x4*>(src + DH / 2);
-    }
+#pragma unroll
+    for (int i = 0; i < kTurns; ++i)
+      if (kAllTurn || krow + kRows * i < kFaK) {
+        const int key = min(t * kFaK + krow + kRows * i, nk - 1);
+        const _Float16* src = k + (int64_t)(k_row0 + key) * ldkv + g_kv * DH + 8 * kpc;
+        kr[i][0] = *reinterpret_cast<const i32x4*>(src);
+        kr[i][1] = *reinterpret_cast<const i32x4*>(src + DH / 2);
+      }
   };
   auto store_keys = [&](int t, uint8_t* base) {
-    if (kAllTurn || krow < kFaK) {
-      f16x8 a = __builtin_bit_cast(f16x8, kr[0]), bb = __builtin_bit_cast(f16x8, kr[1]);
-      fa_rope8(a, bb, t * kFaK + krow, freq + 8 * kpc);
-      _Float16* ks = reinterpret_cast<_Float16*>(base);
-      *reinterpret_cast<f16x8*>(ks + 8 * fa_kslot<DH>(krow, kpc)) = a;
-      *reinterpret_cast<f16x8*>(ks + 8 * fa_kslot<DH>(krow, kpc + PR)) = bb;
-    }
+    _Float16* ks = reinterpret_cast<_Float16*>(base);
+#pragma unroll
+    for (int i = 0; i < kTurns; ++i)
+      if (kAllTurn || krow + kRows * i < kFaK) {
+        const int row = krow + kRows * i;
+        f16x8 a = __builtin_bit_cast(f16x8, kr[i][0]), bb = __builtin_bit_cast(f16x8, kr[i][1]);
+        fa_rope8(a, bb, t * kFaK + row, freq + 8 * kpc);
+        *reinterpret_cast<f16x8*>(ks + 8 * fa_kslot<DH>(row, kpc)) = a;
+        *reinterpret_cast<f16x8*>(ks + 8 * fa_kslot<DH>(row, kpc + PR)) = bb;
+      }
   };
 
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
@@ -255,8 +258,8 @@ prefill_flash_kernel(const _Float16* __restrict__ q, const _Float16* __restrict_
   auto buffer = [&](int i) { return (KSP * (i & 1) + share) * C::kBuf; };
   if (share < n_tiles) {
     if (ROPE) {
-      load_keys(0);
-      store_keys(0, fa_smem);
+      load_keys(share);
+      store_keys(share, fa_smem + buffer(0));
     } else {
       stage(k, koff, share, lds0 + buffer(0));
     }
@@ -270,7 +273,7 @@ prefill_flash_kernel(const _Float16* __restrict__ q, const _Float16* __restrict_
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     const bool more = t + KSP < n_tiles;
     if (more) {
-      if (ROPE) load_keys(t + 1);
+      if (ROPE) load_keys(t + KSP);
       else stage(k, koff, t + KSP, lds0 + buffer(i + 1));
       stage(v, voff, t + KSP, lds0 + buffer(i + 1) + C::kTile);
     }
@@ -370,7 +373,7 @@ prefill_flash_kernel(const _Float16* __restrict__ q, const _Float16* __restrict_
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if (ROPE && more) store_keys(t + 1, fa_smem + buffer(i + 1));
+    if (ROPE && more) store_keys(t + KSP, fa_smem + buffer(i + 1));
   }
 
   if constexpr (KSP > 1) {
@@ -453,31 +456,70 @@ static hipError_t launch_flash(const PrefillAttnArgs& a, const FaCacheArgs& ca, 
 
 bool prefill_attention_supported(int32_t head_dim) { return head_dim == 64 || head_dim == 128; }
 
-// At most half the CUs get 128 queries of a head: then the waves' own latency
-// counts, and prompts of up to 512 tokens take the kernel with shorter chains.
-static bool few_workgroups(const PrefillAttnArgs& a) {
-  return (int64_t)a.batch * a.n_q_heads * ((a.max_seqlen + 127) / 128) <= 128;
+// The forms a prompt's attention is launched in: the short-prompt kernel
+// (flash_short.hip), and this one with four units in four waves (two
+// workgroups per CU cover each other's barriers), four units in two key shares
+// (eight waves: half the chain per workgroup, one workgroup per CU) or eight
+// units (eight waves: the keys of a rotary layer are turned once for all).
+enum FaForm { FA_SHORT, FA_4, FA_4x2, FA_8 };
+
+// Chosen by how many workgroups of four units the call makes (w), the longest
+// prompt (n), and whether query heads share keys (G > 1, where this kernel's
+// units of several heads fill a workgroup that one head of a short prompt
+// leaves half empty).  us, per form, rotary (r) or not (p), heads Hq/Hkv of 128:
+//   up to 128 tokens the short kernel, but for few tokens or grouped heads
+//   over many prompts.  SHORT, 4: 40 heads 8 x 64 r 9.6, 10.2; 40 heads 64 x
+//   128 r 68.9, 74.9; 28/4 32 x 64 r 16.8, 12.5; 28/4 64 x 100 p 29.6, 31.0;
+//   32 heads 64 x 16 p 20.1, 18.5.
+//   w <= 256, no more than one workgroup per CU: a wave's own chain counts.
+//   SHORT, 4x2: 28/4 1 x 300 r 15.2, 16.1; 3 x 384 r 17.9, 19.2; 32 heads
+//   1 x 448 r 19.5, 18.7; 28/4 1 x 1000 r 38.3, 33.1.
+//   w <= 512, up to two: for long prompts still 4x2.  4, 4x2: 28/4 1 x 2000 r
+//   72.7, 62.4; 2 x 640 p 21.3, 18.0; 32 heads 3 x 640 r 31.8, 35.1.
+//   More: 4, which without rotary embedding always is within 20% of the best;
+//   SHORT only where its tiles of 128 queries have no idle ones.  SHORT, 4:
+//   32 heads 12 x 256 p 24.5, 28.9; 32 x 256 p 59.2, 54.8; 16 x 384 p 48.9,
+//   55.1; 12 x 200 p 23.6, 23.4.
+//   Rotary, 8 where that leaves few units without queries: 4, 8: 32 heads
+//   2 x 1500 77.6, 67.8; 4 x 800 53.1, 55.4; 4 x 640 37.4, 42.1; 28/4 8 x 640
+//   62.3, 55.9; 40 heads 4 x 800 81.1, 69.9.
+static FaForm fa_form(const PrefillAttnArgs& a) {
+  const bool rope = a.rope_theta > 0.f;
+  const int n = a.max_seqlen, G = a.n_q_heads / a.n_kv_heads;
+  const int64_t groups = (int64_t)a.batch * a.n_kv_heads;
+  const int64_t w = groups * fa_workgroups(n, G, 4), w8 = groups * fa_workgroups(n, G, 8);
+  const int64_t tiles = (int64_t)a.batch * a.n_q_heads * (((int64_t)n + 127) / 128);   // of the short kernel
+  if (n <= 128) {
+    if (tiles <= 256) return FA_SHORT;
+    return (!rope && n <= 32) || (G > 1 && (n <= 64 || w <= 512)) ? FA_4 : FA_SHORT;
+  }
+  if (w <= 256) {
+    if (n <= 256 || (n <= 384 && (rope || tiles <= 128))) return FA_SHORT;
+    return n <= 384 ? FA_4 : FA_4x2;
+  }
+  if ((w <= 384 && n > 576) || (w <= 512 && n > 1024)) return FA_4x2;
+  const bool full_tiles = (n - 1) % 128 > 120;
+  if (G == 1 && full_tiles && (n > 256 ? w > 1024 && n <= 384 : !rope && w > 576 && w < 1024)) return FA_SHORT;
+  const bool few_idle = 20 * w8 <= 11 * w;      // at most a tenth more units than with four
+  if (rope && ((w > 1024 && n > 512) || (w > 576 && few_idle && n > (G > 1 ? 256 : 512)))) return FA_8;
+  return FA_4;
 }
 
-template <int DH>
-static hipError_t launch_prefill(const PrefillAttnArgs& a, hipStream_t s) {
+template <int DH, int MODE>
+static hipError_t launch_prefill(const PrefillAttnArgs& a, FaForm f, hipStream_t s) {
   FaCacheArgs none{};
   none.q_len = a.max_seqlen;                // rows past it are left alone
-  // Rotary layers turn the keys once per workgroup, so eight waves take eight
-  // units.  Without that, four: the two workgroups of a CU cover each other's
-  // barriers (four units in two shares of the keys, eight waves: 41 us for the
-  // 4 x 640 prompts, against 28.5).
-  if (a.rope_theta > 0.f) return launch_flash<DH, FA_ROPE, false, 8, 1>(a, none, s);
-  // (Long prompts of few heads have too few workgroups for two per CU, and
-  // there the shares halve the longest one: 1500 tokens of 4 heads 27.3, 21.0 us.)
-  if (few_workgroups(a)) return launch_flash<DH, FA_PLAIN, false, 8, 2>(a, none, s);
-  return launch_flash<DH, FA_PLAIN, false, 4, 1>(a, none, s);
+  if constexpr (MODE == FA_ROPE)
+    if (f == FA_8) return launch_flash<DH, MODE, false, 8, 1>(a, none, s);
+  return f == FA_4x2 ? launch_flash<DH, MODE, false, 8, 2>(a, none, s) : launch_flash<DH, MODE, false, 4, 1>(a, none, s);
 }
 
 hipError_t launch_prefill_attention(const PrefillAttnArgs& a, hipStream_t s) {
   if (a.batch == 0 || a.max_seqlen == 0) return hipSuccess;
-  if (few_workgroups(a) && a.max_seqlen <= 512) return launch_prefill_attention_short(a, s);
-  return a.head_dim == 128 ? launch_prefill<128>(a, s) : launch_prefill<64>(a, s);
+  const FaForm f = fa_form(a);
+  if (f == FA_SHORT) return launch_prefill_attention_short(a, s);
+  if (a.rope_theta > 0.f) return a.head_dim == 128 ? launch_prefill<128, FA_ROPE>(a, f, s) : launch_prefill<64, FA_ROPE>(a, f, s);
+  return a.head_dim == 128 ? launch_prefill<128, FA_PLAIN>(a, f, s) : launch_prefill<64, FA_PLAIN>(a, f, s);
 }
 
 // Rebuilt keys turned in place at their positions, for layers with rotary

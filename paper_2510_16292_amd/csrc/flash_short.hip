@@ -1,15 +1,13 @@
 // Causal self-attention of short prompts: the same product as flash.hip, for
-// calls whose queries make few workgroups.
+// the calls sent here by fa_form there (few workgroups, or up to 128 tokens;
+// its comment has the figures of both).
 //
 // One workgroup of eight waves takes 128 consecutive queries of one
 // (sequence, query head); wave w owns the 16-query block q0 + 16w .. +15.
 // With half the queries per wave of flash.hip's units every LDS read serves
 // half the products, but a wave's chain through a tile (scores, softmax,
-// output) is half as long and the queries spread over twice the waves, which
-// is what counts while most of the chip is idle.  us, here and with those
-// units: 28 heads over 4, 40 tokens 5.8, 6.4 (rotary 6.7, 9.1); 2 x 100 tokens
-// of 32 heads 6.9, 7.7 (8.5, 9.9); 2 x 200 of 28 over 4 10.3, 10.7 (12.6,
-// 16.1); 4 x 300 of 32 18.1, 14.2 (23.1, 18.9).
+// output) is half as long and twice as many waves fit a CU, which is what
+// counts while the chip is not full or the chains are short.
 //
 // Key/value tiles of 64 tokens are staged in LDS (shared by the waves; the
 // next tile's rows are already in registers while the current one is used).

@@ -655,9 +655,17 @@ def test_prefill_attention_rope_ragged(shape, lengths, theta):
     ((7, 1, 128), [97, 128, 129]),
     ((3, 1, 64), 8 * [31, 32, 33, 63, 64, 65, 1]),   # units of 32 queries and tiles at their edges, one odd group each
     ((7, 1, 128), 7 * [97, 256, 257]),           # seven heads of a group over workgroups of four and eight units
-    ((5, 5, 128), [513, 575]),                   # past the eighth tile (the keys' exact angles are formed anew)
-    ((2, 2, 64), [9] * 70),                      # more (sequence, head) groups than one set of an XCD holds
-], ids=["short-g3", "short-g7", "g3-dh64", "g7-dh128", "mha5-resync", "many-short"])
+    ((5, 5, 128), [513, 575]),                   # past the eighth tile, the last one nearly empty and nearly full
+    ((2, 2, 64), [9] * 70),                      # many sequences of a part of one unit
+    ((4, 2, 64), [9] * 600),                     # more (sequence, head) groups than one set of an XCD holds
+    ((3, 1, 64), 15 * [31, 32, 33, 63, 64, 65, 1]),  # four units per workgroup, grouped heads of short prompts
+    ((2, 2, 64), [33, 128, 127] * 48),           # the short-prompt kernel over many sequences
+    ((8, 8, 64), [256, 255] * 25),               # ... and where its tiles are full
+    ((4, 4, 128), [1100, 64, 65]),               # two key shares over long prompts, an odd and an even number of tiles
+    ((7, 1, 128), [290, 97] * 17),               # eight units per workgroup (rotary), heads of one group over several
+    ((2, 2, 128), [513, 65] + [9] * 101),        # ... and of one head each
+], ids=["short-g3", "short-g7", "g3-dh64", "g7-dh128", "mha5-resync", "many-short", "sets", "units-g3-dh64", "short-many",
+        "short-full", "shares", "eight-g7", "eight-mha"])
 def test_prefill_attention_unit_edges(shape, lengths, theta):
     """Prefill attention where its units (32 queries of a head), key tiles,
     workgroups and workgroup order have their edges, against the oracle."""

@@ -524,43 +524,78 @@ hipError_t launch_prefill_attention(const PrefillAttnArgs& a, hipStream_t s) {
 
 // Rebuilt keys turned in place at their positions, for layers with rotary
 // embedding: thread (position t, pair run) of a sequence turns that run in
-// every key/value head.  Once per call, where the attention's workgroups (28
-// per sequence and key/value head for 100 queries of 7 heads each) would each
-// turn every key they read.
+// kRkHeads key/value heads (blockIdx.z: which).  Once per call, where the
+// attention's workgroups (28 per sequence and key/value head for 100 queries
+// of 7 heads each) would each turn every key they read.
+constexpr int kRkHeads = 4;
+
 template <int DH>
 __global__ void __launch_bounds__(256)
 rope_keys_kernel(_Float16* __restrict__ kv, const int32_t* __restrict__ seq_len, int32_t capacity, int32_t ldkv,
                  int32_t Hkv, double log2_theta) {
   constexpr int PR = DH / 16;
+  __shared__ double freq[DH / 2];
   const int b = blockIdx.y, t = (blockIdx.x * 256 + threadIdx.x) / PR, pc = threadIdx.x % PR;
-  if (t >= min(seq_len[b], capacity)) return;
+  const int g0 = blockIdx.z * kRkHeads;
+  const bool in = t < min(seq_len[b], capacity);
+  _Float16* row = kv + ((int64_t)b * capacity + t) * ldkv + g0 * DH + 8 * pc;
+  f16x8 x[kRkHeads], y[kRkHeads];
+#pragma unroll
+  for (int i = 0; i < kRkHeads; ++i)
+    if (in && g0 + i < Hkv) {
+      x[i] = *reinterpret_cast<const f16x8*>(row + i * DH);
+      y[i] = *reinterpret_cast<const f16x8*>(row + i * DH + DH / 2);
+    }
+  if (threadIdx.x < DH / 2) freq[threadIdx.x] = fa_freq(threadIdx.x, DH, log2_theta);
+  __syncthreads();
   float c[8], sn[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) fa_angle(t, fa_freq(8 * pc + e, DH, log2_theta), &c[e], &sn[e]);
-  _Float16* row = kv + ((int64_t)b * capacity + t) * ldkv + 8 * pc;
-  for (int g = 0; g < Hkv; ++g, row += DH) {
-    f16x8 x = *reinterpret_cast<const f16x8*>(row), y = *reinterpret_cast<const f16x8*>(row + DH / 2);
-    fa_turn8(x, y, c, sn);
-    *reinterpret_cast<f16x8*>(row) = x;
-    *reinterpret_cast<f16x8*>(row + DH / 2) = y;
-  }
+  for (int e = 0; e < 8; ++e) fa_angle(t, freq[8 * pc + e], &c[e], &sn[e]);
+#pragma unroll
+  for (int i = 0; i < kRkHeads; ++i)
+    if (in && g0 + i < Hkv) {
+      fa_turn8(x[i], y[i], c, sn);
+      *reinterpret_cast<f16x8*>(row + i * DH) = x[i];
+      *reinterpret_cast<f16x8*>(row + i * DH + DH / 2) = y[i];
+    }
 }
 
+// Few queries over many keys leave few workgroups: their waves share the keys
+// in two halves (4x2) until there is more than one workgroup of four units per
+// CU, or one where the keys are few.  100 queries of 28 heads over 4, four
+// sequences of 1899 tokens: 87 -> 44 us; whole calls, 4 and 4x2: 160 queries,
+// 1899 tokens, 32 heads, eight sequences 523, 544 (512 workgroups), four 294,
+// 288 (256); 28/4, eight sequences 117, 128 (288); 100 queries, 300 tokens, 32
+// heads, eight sequences 116, 119 (256).
+// The keys of rotary layers are turned in the attention where each is read
+// once (no grouped heads) by enough workgroups, or where they are few.  Whole
+// calls, in it (4x2) and before it: 32 heads, 16 queries, 1899 tokens, one
+// sequence 112, 102, four 256, 265, eight 445, 501; 300 tokens, one sequence
+// 49.4, 50.8; 28/4, 300 tokens 23.6, 26.1, 600 tokens 55.8, 54.2, 1899 tokens
+// 65.3, 53.5.  With a workgroup of eight units for every CU those share them:
+// 32 heads, eight sequences, 4x2 and 8: 160 queries, 1899 tokens 567, 523, 100
+// queries, 300 tokens 124, 121; four sequences (128 workgroups), 160 queries,
+// 1899 tokens 303, 327.
 template <int DH>
 static hipError_t launch_cache(const CacheAttnArgs& c, const PrefillAttnArgs& a, const FaCacheArgs& ca, hipStream_t s) {
-  // Few queries over many keys leave few workgroups: their waves share the
-  // keys in two halves (100 queries of 28 heads over 1899 tokens, 4 sequences:
-  // 87 -> 44 us, and 7 us for turning the keys before).
-  if (c.rope_theta <= 0.f) return launch_flash<DH, FA_PLAIN, true, 8, 2>(a, ca, s);
+  const int G = c.n_q_heads / c.n_kv_heads;
+  const int64_t w = (int64_t)c.batch * c.n_kv_heads * fa_workgroups(c.q_len, G, 4);
+  const int64_t w8 = (int64_t)c.batch * c.n_kv_heads * fa_workgroups(c.q_len, G, 8);
+  const bool filled = w > 256, few_keys = c.max_len <= 512;
+  if (c.rope_theta <= 0.f)
+    return filled || (w == 256 && few_keys) ? launch_flash<DH, FA_PLAIN, true, 4, 1>(a, ca, s) : launch_flash<DH, FA_PLAIN, true, 8, 2>(a, ca, s);
+  if (G == 1 && w8 >= 256) return launch_flash<DH, FA_ROPE, true, 8, 1>(a, ca, s);
+  if (G == 1 ? few_keys || w >= 96 : few_keys && !filled) return launch_flash<DH, FA_ROPE, true, 8, 2>(a, ca, s);
   {
     KernelScope ks("rope_keys", s);
-    const dim3 grid((unsigned)(((int64_t)c.max_len * (DH / 16) + 255) / 256), c.batch);
+    const dim3 grid((unsigned)(((int64_t)c.max_len * (DH / 16) + 255) / 256), c.batch,
+                    (c.n_kv_heads + kRkHeads - 1) / kRkHeads);
     QSVD_LAUNCH(ks, rope_keys_kernel<DH>, grid, dim3(256), 0, s, c.kv, c.seq_len, c.capacity, ca.ldkv, c.n_kv_heads,
                 log2((double)c.rope_theta));
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  return launch_flash<DH, FA_ROPE_Q, true, 8, 2>(a, ca, s);
+  return filled ? launch_flash<DH, FA_ROPE_Q, true, 4, 1>(a, ca, s) : launch_flash<DH, FA_ROPE_Q, true, 8, 2>(a, ca, s);
 }
 
 // Queries of several positions per sequence over a cache's rebuilt K^ | V^

@@ -1805,6 +1805,35 @@ def test_decode_reconstruct_qlen_block(gqa, fmt, theta):
         _check_qlen_block(out.reshape(q.shape), ref, lengths, q_len)
 
 
+@pytest.mark.parametrize("theta", [None, 1.0e4], ids=["plain", "rope"])
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("hq,hkv,lengths,q_len", [
+    (8, 8, [40 + i % 9 for i in range(32)] + [3], 6),    # a workgroup for every CU; one sequence shorter than the block
+    (8, 4, [70 + i for i in range(32)] + [65], 70),      # ... of grouped heads: keys turned before
+    (4, 2, [300, 64, 0], 40),                            # few keys: turned in two shares
+    (8, 8, [600] + [20 + i for i in range(12)], 5),      # many keys, each read once
+    (8, 2, [600, 130, 64], 33),                          # many keys, few workgroups: turned before
+], ids=["filled-mha", "filled-gqa", "few-keys", "mha", "few-wgs"])
+def test_decode_reconstruct_launch_forms(hq, hkv, lengths, q_len, dh, theta):
+    """The full-rebuild form with several queries per sequence in each of its
+    launch forms, against the oracle."""
+    L = configs.LayerShape(d=256, n_q_heads=hq, n_kv_heads=hkv, head_dim=dh, r=128)
+    ol, dl = _random_factor_layer(L, 1700 + hq + dh)
+    wl = configs.Workload(98, "forms", L, "gaussian", 8, 0, 8, O.CACHE_I8)
+    oc, dc = _prefilled_caches(wl, O.CACHE_I8, lengths, max(lengths) + 3)
+    nb = len(lengths)
+    q = (np.random.default_rng(hq + q_len).standard_normal((nb, q_len, hq * dh)) * 2.0).astype(np.float16)
+    ref = np.zeros(q.shape, np.float64)
+    for b, n in enumerate(lengths):
+        k = min(q_len, n)
+        if k:
+            ref[b:b + 1, q_len - k:] = O.attention_reference(ol, oc, q.astype(np.float64)[:, q_len - k:], q_len=k,
+                                                             batches=[b], rope_theta=theta)[b:b + 1]
+    H.say(f"rebuild forms heads={hq}/{hkv} dh={dh} lengths={lengths[:5]} q_len={q_len} theta={theta}")
+    out = H.host(H.decode_attention(dl, dc, H.dev(q), B.QSVD_ATTN_RECONSTRUCT, q_len=q_len, rope_theta=theta))
+    _check_qlen_block(out.reshape(q.shape), ref, lengths, q_len)
+
+
 def test_decode_rope_qlen_llava7b_chunk(llava):
     """A 64-query chunk continuing two LLaVA-7B-shaped sequences (32 heads x
     128, r = 1536, fp16 cache of 200 and 1000 tokens) with rotary embeddings

@@ -27,7 +27,6 @@
 
 #include "common.h"
 #include "launch.h"
-
 #include "rowpass.h"
 
 namespace qsvd {
@@ -212,14 +211,16 @@ skinny_gemm_kernel(const void* __restrict__ a_src, int64_t lda, float clip, cons
       }
     }
   }
+  // (shifted back before the waves' sums are added: the scaled total of a long
+  // contraction would pass 32 bits, 127 * 7 * 16 K from K = 150997)
+  const int sh = (WBITS == 4 ? 4 : 0) + (ASRC == SK_A_I8 && abits == 4 ? 4 : 0);
   if (!gsteps)
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb)
-      if (rb < rbl) red[(w * rbl + rb) * 64 + lane] = acc[rb];
+      if (rb < rbl) red[(w * rbl + rb) * 64 + lane] = acc[rb] >> sh;
   __syncthreads();
 
   // --- epilogue: one thread per output (row m, column n) ------------------------
-  const int sh = (WBITS == 4 ? 4 : 0) + (ASRC == SK_A_I8 && abits == 4 ? 4 : 0);
   for (int t = tid; t < M * cols; t += 64 * nw) {
     const int m = t / cols, nl = t % cols;
     const int32_t nn = blockIdx.x * cols + nl;
@@ -231,7 +232,6 @@ skinny_gemm_kernel(const void* __restrict__ a_src, int64_t lda, float clip, cons
     if (!group) {
       int32_t tot = 0;
       for (int ww = 0; ww < nw; ++ww) tot += red[(ww * rbl + rb) * 64 + src][v];
-      tot >>= sh;
       if (dbg) dbg[(int64_t)m * N + nn] = tot;
       y = mul_rn(mul_rn((float)tot, rs), first ? pre_cs : col_scale[nn]);
     } else {

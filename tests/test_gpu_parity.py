@@ -380,6 +380,36 @@ def test_projection_bitexact_stage_edges(d, r, w_bits, w_group, abits, M):
     _check_mixed(ol, H.Prefill(dl, M, debug=False, abits=abits).run(H.dev(X)).result(), X, abits)
 
 
+def _latent_of_codes(d, r, w_bits, w_group, abits, rows, codes, scales):
+    """C of `rows` rows of ones (activation codes all 127 or 7) through weight
+    codes [r][d] and their scales, as the device forms it."""
+    t = H.torch()
+    a = H.dev(O.pack_int4(codes) if w_bits == 4 else codes)
+    n_up = 3 * 64
+    b = t.zeros((n_up, r if w_bits == 8 else r // 2), dtype=t.int8 if w_bits == 8 else t.uint8, device="cuda")
+    sb = t.ones((r // w_group, n_up) if w_group else (n_up,), device="cuda")
+    dl = B.DeviceLayer.from_device(d, r, 1, 1, 64, w_bits, w_group, a, H.dev(scales), b, sb)
+    p = H.Prefill(dl, rows, mask=B.QSVD_OUT_Q, debug=False, abits=abits)
+    return p.run(t.ones((rows, d), dtype=t.float16, device="cuda")).result()
+
+
+@pytest.mark.parametrize("rows", [1, 17])
+def test_decode_projection_long_contraction(rows):
+    """Few rows with 4-bit activation codes over a contraction of 196608: the
+    integer sums fit 32 bits (|sum| <= 7 * 127 * 196608), sixteen times them
+    would not.  Bit-exact."""
+    d, r = 196608, 64
+    k = np.arange(d)
+    codes = np.stack([np.where(k * r < d * (j + 1), 127, -127) for j in range(r)]).astype(np.int8)
+    sa = np.full(r, 2.0 ** -20, np.float32)
+    H.say(f"long contraction rows={rows}")
+    got = _latent_of_codes(d, r, 8, 0, 4, rows, codes, sa)
+    acc = 7 * codes.astype(np.int64).sum(1)
+    assert 2 ** 31 / 16 < np.abs(acc).max() < 2 ** 31
+    want = ((acc.astype(np.float32) * (np.float32(1.0) / np.float32(7.0))) * sa).astype(np.float16)
+    assert np.array_equal(got["C_h"].view(np.uint16), np.tile(want.view(np.uint16), (rows, 1)))
+
+
 def test_prefill_masks_leave_other_outputs(tiny):
     wl, ol, dl = tiny
     X = gen.fill_activations(wl, 40)

@@ -44,6 +44,7 @@
 
 #include "common.h"
 #include "flash.h"
+#include "flash_map.h"
 #include "launch.h"
 
 namespace qsvd {
@@ -116,24 +117,9 @@ prefill_flash_kernel(const _Float16* __restrict__ q, const _Float16* __restrict_
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hl = lane >> 5;
 
-  // Workgroup -> (sequence, key/value head, NW units).  The workgroups of one
-  // (sequence, key/value head) read the same rows, so they get ids that one
-  // XCD receives (the chip hands workgroup i to XCD i % 8) and share its L2;
-  // the groups go round the XCDs one by one, so that sequences of different
-  // lengths spread over them, in `parts` interleaved parts each where that
-  // makes a multiple of eight.  Within an XCD, sets of so many parts as make
-  // about 128 workgroups (two rounds of its CUs) run one after the other, the
-  // workgroups with most keys of a set first.
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int wpp = (n_wg + parts - 1) / parts;                   // workgroups per part
-  const int ppx = (n_seq * Hkv * parts + 7) / 8;                // parts per XCD
-  const int per_set = max(1, 128 / wpp);
-  const int set = slot / (per_set * wpp), in_set = slot - set * per_set * wpp;
-  const int n_in = min(per_set, ppx - set * per_set);           // parts of this set
-  const int vg = xcd + 8 * (set * per_set + in_set % n_in);
-  const int grp = vg / parts;
-  const int wg = (wpp - 1 - in_set / n_in) * parts + vg % parts;
-  if (grp >= n_seq * Hkv || wg >= n_wg) return;
+  const FaWork work = fa_work(blockIdx.x, n_seq * Hkv, n_wg, parts);
+  if (!work.any) return;
+  const int grp = work.group, wg = work.wg;
   const int b = grp / Hkv, g_kv = grp - b * Hkv, G = Hq / Hkv;
   // this sequence's rows: query i (i < nq) is row q_row0 + i at position
   // q_off + i, key t (t < nk) is row k_row0 + t at position t; query i sees
@@ -444,9 +430,8 @@ static hipError_t launch_flash(const PrefillAttnArgs& a, const FaCacheArgs& ca, 
   if (e != hipSuccess) return e;
   const int n_wg = fa_workgroups(CACHE ? ca.q_len : a.max_seqlen, a.n_q_heads / a.n_kv_heads, C::UW);
   const int64_t groups = (int64_t)a.batch * a.n_kv_heads;
-  int parts = groups % 8 == 0 ? 1 : groups % 4 == 0 ? 2 : groups % 2 == 0 ? 4 : 8;
-  while (parts > n_wg) parts /= 2;
-  const int64_t blocks = (groups * parts + 7) / 8 * 8 * ((n_wg + parts - 1) / parts);
+  const int parts = fa_parts(groups, n_wg);
+  const int64_t blocks = fa_blocks(groups, n_wg, parts);
   KernelScope ks(CACHE ? "cache_flash" : MODE != FA_PLAIN ? "prefill_flash_rope" : "prefill_flash", s);
   QSVD_LAUNCH(ks, kern, dim3((unsigned)blocks), dim3(NW * 64), lds, s, a.q, a.k, a.v, a.cu_seqlens, a.batch,
               a.n_q_heads, a.n_kv_heads, n_wg, parts, a.sm_scale * kFaLog2e,

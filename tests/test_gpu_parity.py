@@ -710,22 +710,34 @@ def test_prefill_attention_unit_edges(shape, lengths, theta):
 
 
 @pytest.mark.parametrize("theta", [None, 1e4], ids=["plain", "rope"])
-def test_prefill_attention_past_max_seqlen(theta):
+@pytest.mark.parametrize("shape,lengths,most", [
+    ((4, 4, 64), [200], 70),                 # the short-prompt kernel
+    ((4, 2, 64), [40] * 70, 30),             # four units per workgroup
+    ((4, 4, 128), [700, 20, 650], 600),      # two key shares
+    ((7, 1, 64), [320, 291, 9] * 12, 290),   # eight units (rotary)
+], ids=["short", "units", "shares", "eight"])
+def test_prefill_attention_past_max_seqlen(shape, lengths, most, theta):
     """Rows past max_seqlen stay as they were, the rows before it do not see them."""
-    hq, hkv, dh, n, most = 4, 4, 64, 200, 70
+    hq, hkv, dh = shape
+    n = sum(lengths)
     Q, K, V = _qkv(395, n, hq, hkv, dh)
     q, k, v = H.dev(Q), H.dev(K), H.dev(V)
-    full = H.host(H.prefill_attention(q, k, v, [n], hq, hkv, dh, rope_theta=theta))
     out = H.dev(np.full((n, hq * dh), 7.0, np.float16))
-    cu = H.dev(np.array([0, n], np.int32))
-    args = (B.ptr(q), B.ptr(k), B.ptr(v), 1, B.ptr(cu), most, hq, hkv, dh, 0.0)
+    cu = H.dev(np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32))
+    args = (B.ptr(q), B.ptr(k), B.ptr(v), len(lengths), B.ptr(cu), most, hq, hkv, dh, 0.0)
+    H.say(f"prefill flash past max_seqlen heads={hq}/{hkv} dh={dh} lengths={lengths[:6]} most={most} theta={theta}")
     if theta:
         B.check(B.qsvd_prefill_attention_rope(*args, theta, B.ptr(out), B.stream_handle()))
     else:
         B.check(B.qsvd_prefill_attention(*args, B.ptr(out), B.stream_handle()))
     got = H.host(out)
-    assert H.close_enough(got[:most], full[:most])[0]
-    assert np.all(got[most:] == 7.0)
+    inside = np.concatenate([np.arange(m) < most for m in lengths])
+    want = O.prefill_attention(Q[inside], K[inside], V[inside], [min(m, most) for m in lengths], hq, hkv, dh,
+                               rope_theta=theta)
+    ok, info = H.close_enough(got[inside], want)
+    H.say(f"  max-abs, rel-L2, rms = {info}")
+    assert ok, info
+    assert np.all(got[~inside] == 7.0)
 
 
 def test_prefill_attention_rope_turns_keys_alike():

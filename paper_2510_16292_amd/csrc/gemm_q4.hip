@@ -245,8 +245,9 @@ gemm_q4_pipe_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B
   };
   // the scales of half h's group for this lane's columns, times 2^-SH:
   // (float)acc * (s_g 2^-SH) is the same real number as (float)(acc >> SH) * s_g
-  // (acc is an exact multiple of 2^SH below 2^24, and scaling s_g by a power of
-  // two is exact), so it rounds the same; the shift is saved on every element
+  // (acc is an exact multiple of 2^SH and acc >> SH, at most 4.2e6 for the
+  // longest groups, 4096, has 24 bits or fewer; scaling s_g by a power of two
+  // is exact), so it rounds the same; the shift is saved on every element
   float gss[TJ];
   auto read_scales = [&](int kt, int h) {
     const float* src = reinterpret_cast<const float*>(q4_smem + (kt % NS) * C::kStage + SA + C::SB + (4 * h + w) * 256);

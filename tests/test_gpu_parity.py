@@ -410,6 +410,22 @@ def test_decode_projection_long_contraction(rows):
     assert np.array_equal(got["C_h"].view(np.uint16), np.tile(want.view(np.uint16), (rows, 1)))
 
 
+@pytest.mark.parametrize("w_bits,abits", [(4, 8), (4, 4), (8, 4)])
+def test_projection_large_group_sums(w_bits, abits):
+    """One scale group of 2048: 16 (256) times its sums pass 2^24.  Bit-exact."""
+    d = r = 2048
+    qa, qw = (127 if abits == 8 else 7), (7 if w_bits == 4 else 127)
+    k = np.arange(d)
+    codes = np.stack([np.where(k < d - j % 700, qw, qw - 1 - j % 5) for j in range(r)]).astype(np.int8)
+    sg = (2.0 ** -18 * (1.0 + np.arange(r) / r)).astype(np.float32)[None]
+    H.say(f"large groups w{w_bits} a{abits}")
+    got = _latent_of_codes(d, r, w_bits, 2048, abits, 40, codes, sg)
+    acc = qa * codes.astype(np.int64).sum(1)
+    assert np.abs(acc).max() * (16 if w_bits == 4 else 1) * (16 if abits == 4 else 1) > 2 ** 24
+    want = ((acc.astype(np.float32) * sg[0]) * (np.float32(1.0) / np.float32(qa))).astype(np.float16)
+    assert np.array_equal(got["C_h"].view(np.uint16), np.tile(want.view(np.uint16), (40, 1)))
+
+
 def test_prefill_masks_leave_other_outputs(tiny):
     wl, ol, dl = tiny
     X = gen.fill_activations(wl, 40)

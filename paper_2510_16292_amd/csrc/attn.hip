@@ -333,16 +333,35 @@ __device__ __forceinline__ ChunkPlan plan_chunks(const int32_t* __restrict__ seq
   return p;
 }
 
-// The sequence of a slot (batch: none), its length and the chunk's number in it.
-struct SlotChunk {
-  int b, len, ch;
+// The id-th piece of work: query qi of sequence b over the rows of its chunk
+// `ch` (no more work: b == batch).  All queries of a sequence come before the
+// next sequence's, so that those at work together share its rows in the caches
+// (query by query over all sequences, four sequences of up to 3000 rows, 120
+// queries each, took 384 us for 329).
+struct ChunkWork {
+  int b, qi, ch, slot, len, chunk;    // slot: the chunk among all; len: rows of the sequence
 };
-__device__ __forceinline__ SlotChunk slot_chunk(const ChunkPlan& p, int32_t batch, int slot) {
+__device__ __forceinline__ ChunkWork chunk_work(const int32_t* __restrict__ seq_len, int32_t capacity,
+                                                const ChunkCut& c, int32_t q_len, int id) {
   const int lane = threadIdx.x & 63;
-  SlotChunk o;
-  o.b = __builtin_amdgcn_readfirstlane((int)__popcll(__ballot(lane < batch && p.upto <= slot)));
-  o.len = __builtin_amdgcn_readlane(p.len, o.b & 63);
-  o.ch = slot - (o.b > 0 ? __builtin_amdgcn_readlane(p.upto, (o.b - 1) & 63) : 0);
+  ChunkWork o{};
+  if (c.n_even == 1) {                // a chunk holds any sequence
+    o.b = o.slot = q_len == 1 ? id : id / q_len;
+    o.qi = id - o.b * q_len;
+    o.chunk = c.even;
+    o.len = o.b < c.batch ? min(seq_len[o.b], capacity) : 0;
+    return o;
+  }
+  const ChunkPlan p = plan_chunks(seq_len, capacity, c);
+  o.b = __builtin_amdgcn_readfirstlane((int)__popcll(__ballot(lane < c.batch && p.upto * q_len <= id)));
+  if (o.b >= c.batch) return o;
+  const int first = o.b > 0 ? __builtin_amdgcn_readlane(p.upto, o.b - 1) : 0;
+  const int n = __builtin_amdgcn_readlane(p.upto, o.b) - first, i = id - first * q_len;
+  o.qi = q_len == 1 ? 0 : i / n;
+  o.ch = i - o.qi * n;
+  o.slot = first + o.ch;
+  o.len = __builtin_amdgcn_readlane(p.len, o.b);
+  o.chunk = p.chunk;
   return o;
 }
 
@@ -391,16 +410,14 @@ latent_attn_kernel(const _Float16* __restrict__ qt, const uint8_t* __restrict__ 
   // tokens whose scores it holds).
   float* scl = reinterpret_cast<float*>(smem + NW * 32 * CST * 2 + (PRE ? 0 : (size_t)(NW + 1) * 1024 * 4)) + w * 32;
 
-  // Workgroup (slot, query i): query i of the slot's sequence b (q_len queries
-  // per sequence, the last q_len cached positions) sees positions
-  // [0, L - q_len + i], causally.  Decode has q_len = 1.
-  const int qi = blockIdx.y;
-  const ChunkPlan plan = plan_chunks(seq_len, capacity, cut);
-  const SlotChunk sc = slot_chunk(plan, cut.batch, blockIdx.x);
-  if (sc.b >= cut.batch) return;
-  const int b = sc.b, vb = b * q_len + qi, chunk = plan.chunk;
-  const int L = sc.len - (q_len - 1 - qi);
-  const int t_begin = sc.ch * chunk;
+  // Query i of a sequence (q_len queries per sequence, the last q_len cached
+  // positions) sees positions [0, L - q_len + i], causally.  Decode has
+  // q_len = 1.
+  const ChunkWork wk = chunk_work(seq_len, capacity, cut, q_len, blockIdx.y * gridDim.x + blockIdx.x);
+  if (wk.b >= cut.batch) return;
+  const int b = wk.b, qi = wk.qi, vb = b * q_len + qi, chunk = wk.chunk;
+  const int L = wk.len - (q_len - 1 - qi);
+  const int t_begin = wk.ch * chunk;
   if (t_begin >= L) return;
   const int t_end = min(L, t_begin + chunk);
   const int slice0 = w * RW;
@@ -755,7 +772,7 @@ latent_attn_kernel(const _Float16* __restrict__ qt, const uint8_t* __restrict__ 
   }
   }
 
-  const int64_t part = (int64_t)qi * cut.stride + blockIdx.x;
+  const int64_t part = (int64_t)qi * cut.stride + wk.slot;
   if (w == 0 && lane < 32) {
     ml_part[part * 64 + l32] = m_run;
     ml_part[part * 64 + 32 + l32] = l_run;
@@ -1059,12 +1076,12 @@ latent_attn_h16_kernel(const _Float16* __restrict__ qt, const uint8_t* __restric
   f32x4* ssum = spart + NB * NW * 64;
 
   const int n_hb = hp >> 4;
-  // Workgroup -> (query qi, head block hb, slot).  The n_hb head blocks of one
-  // (qi, slot) read the same cache rows, so they get ids
-  // that one XCD receives together (the chip dispatches the i-th workgroup,
+  // Workgroup -> (piece of work, head block hb).  The n_hb head blocks of one
+  // piece read the same cache rows, so they get ids that one XCD receives
+  // together (the chip dispatches the i-th workgroup,
   // x fastest, to XCD i % 8) and share its L2 instead of each XCD fetching
   // the rows again.  A bijection on the grid.
-  const int n_launch = gridDim.x, pairs = gridDim.x * gridDim.y / n_hb;
+  const int pairs = gridDim.x * gridDim.y / n_hb;
   const int lin = blockIdx.y * gridDim.x + blockIdx.x;
   int pair, hb;
   if (pairs % 8 == 0) {
@@ -1075,13 +1092,11 @@ latent_attn_h16_kernel(const _Float16* __restrict__ qt, const uint8_t* __restric
     pair = lin / n_hb;
     hb = lin % n_hb;
   }
-  const int qi = pair / n_launch, slot = pair % n_launch;
-  const ChunkPlan plan = plan_chunks(seq_len, capacity, cut);
-  const SlotChunk sc = slot_chunk(plan, cut.batch, slot);
-  if (sc.b >= cut.batch) return;
-  const int b = sc.b, vb = b * q_len + qi, chunk = plan.chunk;
-  const int L = sc.len - (q_len - 1 - qi);
-  const int t_begin = sc.ch * chunk;
+  const ChunkWork wk = chunk_work(seq_len, capacity, cut, q_len, pair);
+  if (wk.b >= cut.batch) return;
+  const int b = wk.b, qi = wk.qi, vb = b * q_len + qi, chunk = wk.chunk;
+  const int L = wk.len - (q_len - 1 - qi);
+  const int t_begin = wk.ch * chunk;
   if (t_begin >= L) return;
   const int t_end = min(L, t_begin + chunk);
   // this wave's latent units [u0, u0 + nu) of 128 columns: nu is UMAX or UMAX - 1
@@ -1090,7 +1105,7 @@ latent_attn_h16_kernel(const _Float16* __restrict__ qt, const uint8_t* __restric
   const int slice0 = 128 * u0;
   const int l16 = lane & 15;
   const _Float16* qrow = qt + ((int64_t)vb * hp + hb * 16 + l16) * r + slice0;
-  const int64_t part = (int64_t)(qi * n_hb + hb) * cut.stride + slot;
+  const int64_t part = (int64_t)(qi * n_hb + hb) * cut.stride + wk.slot;
   _Float16* op = o_part + part * (int64_t)r * 16;
   float* mlp = ml_part + part * 32;
   const int64_t seq_row0 = (int64_t)b * capacity;
@@ -1135,10 +1150,18 @@ merge_latent_kernel(const _Float16* __restrict__ o_part, const float* __restrict
   const int row = blockIdx.y, vb = row / n_hb, hb = row - vb * n_hb, tid = threadIdx.x;
   const int cg = CG == 1 ? 0 : tid / TPG, gt = tid % TPG;
   const int b = vb / q_len, qi = vb - b * q_len;
-  const ChunkPlan plan = plan_chunks(seq_len, capacity, cut);
-  const int L = __builtin_amdgcn_readlane(plan.len, b) - (q_len - 1 - qi);
-  const int first = b > 0 ? __builtin_amdgcn_readlane(plan.upto, b - 1) : 0;
-  const int nv = L > 0 ? min(min(chunks_of(L, plan.chunk), n_launched - first), kMaxChunks) : 0;
+  int len, first = b, chunk = cut.even, most = 1;
+  if (cut.n_even == 1) {
+    len = min(seq_len[b], capacity);
+  } else {
+    const ChunkPlan plan = plan_chunks(seq_len, capacity, cut);
+    len = __builtin_amdgcn_readlane(plan.len, b);
+    first = b > 0 ? __builtin_amdgcn_readlane(plan.upto, b - 1) : 0;
+    chunk = plan.chunk;
+    most = min(n_launched - first, kMaxChunks);
+  }
+  const int L = len - (q_len - 1 - qi);
+  const int nv = L > 0 ? min(chunks_of(L, chunk), most) : 0;
   const int64_t pb = (int64_t)(qi * n_hb + hb) * cut.stride + first;
   // element e8 (8 halves): latent quad x4 = e8 / (HB / 2), heads 2*(e8 % (HB / 2)) and +1;
   // the first batch of partial loads goes out before the weights are known
@@ -1453,7 +1476,8 @@ static AbsorbPlan plan_absorbed(const qsvd_layer& w, const qsvd_cache& c, int32_
   k.gran = p.hb == kHeadBlk ? 32 : 64;
   k.batch = c.batch;
   k.stride = c.batch * p.n0;
-  k.slots = std::min(k.stride, kMaxChunks);
+  // at most a workgroup per CU where the sequences leave room for that
+  k.slots = std::min(std::min(k.stride, kMaxChunks), std::max(c.batch, 256 / (q_len * p.n_hb)));
   k.even = ((len + p.n0 - 1) / p.n0 + even_gran - 1) / even_gran * even_gran;
   k.n_even = (len + k.even - 1) / k.even;
   k.even_lo = k.n_even > 1 ? k.even * (k.n_even - 1) : -1;

@@ -1485,8 +1485,9 @@ def test_prefill_attention_wide_int4(fmt=O.CACHE_I4):
     ([0, 700, 0, 64, 0], 1),                                 # empty sequences between
     ([31 + 13 * i for i in range(64)], 1),                   # the most sequences, four chunks each on average
     ([40 + 29 * i for i in range(20)], 13),                  # more query rows than CUs: one chunk a sequence
+    ([900, 700, 130, 1], 33), ([2000, 90], 17),              # a few chunks a sequence, all of its queries in turn
     ([300, 5, 900], 7),                                      # several queries, one sequence shorter than the block
-], ids=["one", "tile1", "skewed", "empty", "b64", "rows260", "q7"])
+], ids=["one", "tile1", "skewed", "empty", "b64", "rows260", "q33", "q17", "q7"])
 @pytest.mark.parametrize("hq", [8, 40], ids=["h32blk", "h16blk"])
 def test_decode_chunks_over_ragged_lengths(lengths, q_len, hq):
     """The absorbed form's context chunks, cut on the device from the lengths,

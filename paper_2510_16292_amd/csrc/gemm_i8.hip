@@ -178,6 +178,30 @@ gemm_i8_pipe_kernel(const int8_t* __restrict__ A, const int8_t* __restrict__ B,
     }
   };
 
+  // RS: the rows of this wave's part of the score epilogue (below), LPR lanes
+  // per row: their sequences and positions, and, like the scales, the lengths
+  // before the stage loads, so that the epilogue does not wait for them.  One
+  // 64-bit division per lane; the steps' rows follow one another.
+  constexpr int RH = RS > 0 ? RS : 128;
+  constexpr int half = RH / 2, LPR = RH / 8, RPS = 64 / LPR;     // lanes per row, rows per step
+  constexpr int RW = BM / C::kWaves, STEPS = RW / RPS;           // rows of the wave
+  static_assert(RW % RPS == 0 && (RS == 0 || BN % RH == 0) && half % 4 == 0, "whole steps, whole heads");
+  const int row0 = w * RW + lane / LPR;
+  int row_b[RS > 0 ? STEPS : 1], row_t[RS > 0 ? STEPS : 1], row_l[RS > 0 ? STEPS : 1];
+  if constexpr (RS > 0) {
+    const int64_t bt0 = re.row0 + min(m0 + row0, M - 1);
+    int b = (int)(bt0 / re.capacity), t = (int)(bt0 - (int64_t)b * re.capacity);
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+      const bool in = m0 + row0 + s * RPS < M;
+      if (s > 0 && in)
+        for (t += RPS; t >= re.capacity; t -= re.capacity) ++b;
+      row_b[s] = b;
+      row_t[s] = t;
+      row_l[s] = in ? re.seq_len[b] : 0;
+    }
+  }
+
   // Scales first, into a register: their wait then leaves the stage loads in
   // flight (fp16 operands: a NULL scale vector means no scale).
   static_assert(BM + BN <= C::kThreads, "at most one scale per thread");
@@ -188,6 +212,11 @@ gemm_i8_pipe_kernel(const int8_t* __restrict__ A, const int8_t* __restrict__ B,
   for (int st = 0; st < NS - 1; ++st)
     if (st < nk) issue(st);
   if (tid < BM + BN) (tid < BM ? s_rs[tid] : s_cs[tid - BM]) = sv;
+  if constexpr (RS > 0) {
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s)
+      if (row_t[s] >= min(row_l[s], re.capacity)) row_b[s] = -1;   // no score wanted
+  }
 
   Acc acc[TI][TJ];
 #pragma unroll
@@ -312,20 +341,11 @@ gemm_i8_pipe_kernel(const int8_t* __restrict__ A, const int8_t* __restrict__ B,
     // 150 of them here, against 892), kept for every head of the tile.  The
     // staged element (row, col) sits in the LDS rows of wave (row / WM, col / WN).
     __syncthreads();
-    constexpr int half = RS / 2, LPR = RS / 8, RPS = 64 / LPR;   // lanes per row, rows per step
-    constexpr int RW = BM / C::kWaves, STEPS = RW / RPS;         // rows of the wave
-    static_assert(RW % RPS == 0 && BN % RS == 0 && half % 4 == 0, "whole steps, whole heads");
     const int li = lane % LPR, j4 = 4 * li;
-    int row_b[STEPS];                                            // sequence, -1: no score wanted
     f32x4 tb[STEPS][2];
-    const int row0 = w * RW + lane / LPR;
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) {
-      const int64_t m = m0 + row0 + s * RPS;
-      const int64_t bt = re.row0 + min(m, M - 1);
-      const int b = (int)(bt / re.capacity), t = (int)(bt - (int64_t)b * re.capacity);
-      row_b[s] = m < M && t < min(re.seq_len[b], re.capacity) ? b : -1;
-      const f32x4* src = reinterpret_cast<const f32x4*>(re.rope + (int64_t)(row_b[s] < 0 ? 0 : t) * half + j4);
+      const f32x4* src = reinterpret_cast<const f32x4*>(re.rope + (int64_t)(row_b[s] < 0 ? 0 : row_t[s]) * half + j4);
       tb[s][0] = src[0];
       tb[s][1] = src[1];
     }

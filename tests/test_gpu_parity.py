@@ -1822,6 +1822,32 @@ def test_decode_rope_latent_short_lengths(fmt):
         assert np.array_equal(out.view(np.uint16), again.view(np.uint16)), (shape, "not deterministic")
 
 
+@pytest.mark.parametrize("fmt", [O.CACHE_F16, O.CACHE_I8], ids=["f16", "i8"])
+@pytest.mark.parametrize("shape", [(8, 2, 32), (8, 4, 64), (4, 2, 128)], ids=["dh32", "dh64", "dh128"])
+@pytest.mark.parametrize("cap,lengths", [
+    (5, [5, 4, 0, 5, 1, 3, 5] + [4] * 30),        # several sequences within a step of the score epilogue's rows
+    (3, [3]), (131, [131, 130, 100, 131]),        # one short one; a tile over two sequences
+], ids=["cap5", "cap3", "cap131"])
+def test_decode_rope_scores_sequence_edges(cap, lengths, shape, fmt):
+    """The rebuild's score epilogue where a wave's rows cross from one sequence
+    to the next, or several, against the oracle."""
+    hq, hkv, dh = shape
+    L = configs.LayerShape(d=256, n_q_heads=hq, n_kv_heads=hkv, head_dim=dh, r=128)
+    ol, dl = _random_factor_layer(L, 1900 + dh)
+    wl = configs.Workload(97, "rope-edges", L, "gaussian", 8, 0, 8, fmt)
+    oc, dc = _prefilled_caches(wl, fmt, lengths, cap)
+    nb = len(lengths)
+    q = (np.random.default_rng(dh + cap).standard_normal((nb, hq * dh)) * 4.0).astype(np.float16)
+    ref = np.zeros(q.shape, np.float64)
+    for b, n in enumerate(lengths):
+        if n:
+            ref[b] = O.attention_reference(ol, oc, q.astype(np.float64)[:, None, :], 1, batches=[b],
+                                           rope_theta=1.0e4)[b, 0]
+    H.say(f"rope scores edges cap={cap} heads={hq}/{hkv} dh={dh} fmt={fmt}")
+    out = H.host(H.decode_attention(dl, dc, H.dev(q), B.QSVD_ATTN_ABSORBED, rope_theta=1.0e4))
+    _check_qlen_block(out.reshape(nb, 1, hq * dh), ref[:, None, :], lengths, 1)
+
+
 def _check_qlen_block(out, ref, lengths, q_len):
     """Rows with a visible position against the oracle; rows whose position
     precedes the cache (a sequence shorter than the query block) are zeros."""

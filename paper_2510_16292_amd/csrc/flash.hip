@@ -10,7 +10,7 @@
 // The unit of work is a wave: 32 consecutive queries of one query head.  The
 // units of one (sequence, key/value head) are numbered query block by query
 // block, the G = Hq / Hkv heads of a block next to each other, and a workgroup
-// takes NW consecutive ones: they read the same key/value tiles, and with
+// takes four or eight consecutive ones: they read the same key/value tiles, and with
 // grouped heads they sit at (nearly) the same positions, so little is computed
 // past the diagonal.  Key/value tiles of 64 tokens are staged in LDS for the
 // workgroup, double-buffered (one barrier per tile): the values, and the keys
@@ -32,8 +32,8 @@
 // and about ten operations per pair of scores and lane: 1.6 times the
 // products' cycles), so the rest is kept few.  Measured against units of 16
 // queries on the 16x16x32 products with one tile buffer: 4 x 640 tokens, 32
-// heads: 38.2 -> 28.5 us; six rotary prompts of 1477 to 2531 tokens, 28 heads
-// over 4: 541 -> 294 us (607 TFLOP/s).
+// heads: 37.8 -> 28.3 us; six rotary prompts of 1477 to 2531 tokens, 28 heads
+// over 4: 541 -> 301 us (593 TFLOP/s).
 //
 // Rotary layers (ROPE): a query row is turned once, in registers, at its
 // position within the sequence; a key row is turned while its tile moves from

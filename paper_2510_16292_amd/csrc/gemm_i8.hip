@@ -337,8 +337,8 @@ gemm_i8_pipe_kernel(const int8_t* __restrict__ A, const int8_t* __restrict__ B,
     // Rotary scores of the tile's rows, RS = head_dim.  A wave takes rows of
     // the tile, LPR lanes per row with four pairs each: a row's (cos, sin) are
     // then one contiguous load per lane group (a lane per row read a line of
-    // its own for every 16 bytes: a 65792 x 4096 x 1536 rebuild took 950 us,
-    // 150 of them here, against 892), kept for every head of the tile.  The
+    // its own for every 16 bytes: a 65792 x 4096 x 1536 rebuild took 929 us,
+    // against 831), kept for every head of the tile.  The
     // staged element (row, col) sits in the LDS rows of wave (row / WM, col / WN).
     __syncthreads();
     const int li = lane % LPR, j4 = 4 * li;

@@ -278,16 +278,22 @@ absorb_kernel(const _Float16* __restrict__ q, const uint8_t* __restrict__ bt, co
 // cuts it anew: T rows in all, chunks of T / (slots - batch / 2) rows first
 // (a sequence's last chunk is half empty on average), then at most two larger
 // lengths, the second T / (slots - batch), which always makes at most `slots`
-// chunks; never more than the host's.  The smallest length that fits may be up
-// to a step below the one found: not searched for, since every workgroup waits
-// for the cut before its first cache address (a search over exact lengths
-// took 0.5 .. 1 us per launch, twice per call).
+// chunks; never more than the host's, and none that cuts the longest sequence
+// finer than the merge takes in one round trip or the host's cut does (one of
+// 3000 rows beside 15 of 150, in 94 chunks: the merge lost more than the
+// chunks gained).  The smallest length that fits may be up to a step below the
+// one found: not searched for, since every workgroup waits for the cut before
+// its first cache address (a search over exact lengths took 0.5 .. 1 us per
+// launch, twice per call).
 // ---------------------------------------------------------------------------
+constexpr int kMergeBatch = 16;   // chunk partials a merge thread has in flight (one round trip for <= 16 chunks)
+
 struct ChunkCut {
   int32_t batch, stride;            // sequences, slots of one query and head block in the partials
   int32_t slots, gran;              // slots of the cut from all lengths, its chunks' granularity
   int32_t even, n_even, even_lo;    // the host's cut; it serves lengths in (even_lo, even * n_even]
   float inv_mid, inv_step;          // rows -> first chunk length, half the way from there to the last
+  float inv_most;                   // longest sequence -> least chunk length
 };
 
 // inclusive sum over the lanes below and this one
@@ -298,6 +304,17 @@ __device__ __forceinline__ int lanes_scan(int x) {
   x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
   x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast 15, 31
   x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+  return x;
+}
+
+// ... and their maximum (values >= 0), in the last lane.
+__device__ __forceinline__ int lanes_max(int x) {
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
   return x;
 }
 
@@ -320,13 +337,16 @@ __device__ __forceinline__ ChunkPlan plan_chunks(const int32_t* __restrict__ seq
   p.chunk = c.even;
   p.upto = (lane + 1) * c.n_even;
   if (!__any(lane < c.batch && (p.len <= c.even_lo || p.len > c.even * c.n_even))) return p;
-  const float rows = (float)(uint32_t)__builtin_amdgcn_readlane(lanes_scan(p.len), 63);
-  // (gran is a power of two; at least one gran)
-  auto up = [&](float x) { return (max((int)__builtin_ceilf(x), 1) + c.gran - 1) & -c.gran; };
-  const int step = up(rows * c.inv_step);
-  for (p.chunk = up(rows * c.inv_mid); p.chunk < c.even; p.chunk += step) {
-    p.upto = lanes_scan(chunks_of(p.len, p.chunk));
-    if (__builtin_amdgcn_readlane(p.upto, 63) <= c.slots) return p;
+  if (c.even > c.gran) {
+    const float rows = (float)(uint32_t)__builtin_amdgcn_readlane(lanes_scan(p.len), 63);
+    const float most = (float)__builtin_amdgcn_readlane(lanes_max(p.len), 63);
+    // (gran is a power of two; at least one gran)
+    auto up = [&](float x) { return (max((int)__builtin_ceilf(x), 1) + c.gran - 1) & -c.gran; };
+    const int step = up(rows * c.inv_step);
+    for (p.chunk = up(fmaxf(rows * c.inv_mid, most * c.inv_most)); p.chunk < c.even; p.chunk += step) {
+      p.upto = lanes_scan(chunks_of(p.len, p.chunk));
+      if (__builtin_amdgcn_readlane(p.upto, 63) <= c.slots) return p;
+    }
   }
   p.chunk = c.even;
   p.upto = lanes_scan(chunks_of(p.len, p.chunk));
@@ -1134,7 +1154,6 @@ latent_attn_h16_kernel(const _Float16* __restrict__ qt, const uint8_t* __restric
 // walks all the chunks, and CG 8 makes eight times as many.
 // ---------------------------------------------------------------------------
 constexpr int kMergeElems = 2048;
-constexpr int kMergeBatch = 16;   // chunk partials in flight per thread (one round trip for <= 16 chunks)
 constexpr int kMergeWBatch = 4;   // (m, l) pairs in flight per lane in the weights phase
 
 template <int HB, int CG>
@@ -1448,6 +1467,17 @@ static bool pick_slice(int r, int* rw, int* nw) {
 // The 16-head kernel takes r a multiple of 128 up to 3 * 128 columns per wave.
 static bool h16_rank_ok(int r) { return r % 128 == 0 && r / 128 <= 3 * kH16Waves; }
 
+// Chunk groups per merge workgroup: eight (four) where one would leave three
+// CUs in four (half the CUs) without a workgroup and a thread's loads of all
+// its chunks are more than one batch.  One sequence of 1502 tokens, r = 1536
+// (94 chunks): 22.1 us with one group, 10.5 with eight; 32 sequences of 301
+// tokens, r = 128 (at most 8 chunks each): 4.1 with one, 5.4 with eight.
+static int merge_groups(int r, int hb, int64_t grows, int per_seq) {
+  const int64_t wgs = (int64_t)((r * hb + kMergeElems - 1) / kMergeElems) * grows;
+  if (per_seq < kMergeBatch || wgs > 128) return 1;
+  return wgs <= 64 ? 8 : 4;
+}
+
 static AbsorbPlan plan_absorbed(const qsvd_layer& w, const qsvd_cache& c, int32_t q_len) {
   AbsorbPlan p{};
   if (w.n_q_heads <= kHeadBlk && pick_slice(w.r, &p.rw, &p.nw)) {
@@ -1478,8 +1508,12 @@ static AbsorbPlan plan_absorbed(const qsvd_layer& w, const qsvd_cache& c, int32_
   k.stride = c.batch * p.n0;
   // at most a workgroup per CU where the sequences leave room for that
   k.slots = std::min(std::min(k.stride, kMaxChunks), std::max(c.batch, 256 / (q_len * p.n_hb)));
+  // (more workgroups than CUs where n0 was rounded up, 40 sequences of 3000
+  // rows in 7 chunks each 91 us, in 6 chunks 66: but fewer partials again, and
+  // at 20 sequences of 1000 rows in 11 chunks for 13 the error grew by 0.7%)
   k.even = ((len + p.n0 - 1) / p.n0 + even_gran - 1) / even_gran * even_gran;
   k.n_even = (len + k.even - 1) / k.even;
+  k.inv_most = 1.f / std::max(p.n0, kMergeBatch * merge_groups(w.r, p.hb, grows, p.n0));
   k.even_lo = k.n_even > 1 ? k.even * (k.n_even - 1) : -1;
   k.inv_mid = 1.f / (k.slots - c.batch / 2);
   // (a little over: at the second step the fit is certain)
@@ -1625,19 +1659,13 @@ static hipError_t launch_merge_groups(const AttnArgs& a, const AbsorbPlan& p, in
   return hipGetLastError();
 }
 
-// Chunk groups per merge workgroup: eight (four) where one would leave three
-// CUs in four (half the CUs) without a workgroup and a thread's loads of all
-// its chunks are more than one batch.  One sequence of 1502 tokens, r = 1536
-// (94 chunks): 22.1 us with one group, 10.5 with eight; 32 sequences of 301
-// tokens, r = 128 (at most 8 chunks each): 4.1 with one, 5.4 with eight.
 template <int HB>
 static hipError_t launch_merge(const AttnArgs& a, const AbsorbPlan& p, int32_t rows, const _Float16* opart,
                                const float* ml, _Float16* olat, hipStream_t s) {
-  const qsvd_cache& c = *a.c;
-  const int64_t wgs = (int64_t)((a.w->r * HB + kMergeElems - 1) / kMergeElems) * rows * p.n_hb;
-  const int per_seq = p.n_launched / c.batch;      // chunks of a sequence, on average at most
-  if (wgs <= 64 && per_seq >= kMergeBatch) return launch_merge_groups<HB, 8>(a, p, rows, opart, ml, olat, s);
-  if (wgs <= 128 && per_seq >= kMergeBatch) return launch_merge_groups<HB, 4>(a, p, rows, opart, ml, olat, s);
+  // (the chunks of a sequence, on average at most)
+  const int cg = merge_groups(a.w->r, HB, (int64_t)rows * p.n_hb, p.n_launched / a.c->batch);
+  if (cg == 8) return launch_merge_groups<HB, 8>(a, p, rows, opart, ml, olat, s);
+  if (cg == 4) return launch_merge_groups<HB, 4>(a, p, rows, opart, ml, olat, s);
   return launch_merge_groups<HB, 1>(a, p, rows, opart, ml, olat, s);
 }
 

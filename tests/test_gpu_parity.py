@@ -1515,13 +1515,18 @@ def test_decode_chunks_over_ragged_lengths(lengths, q_len, hq):
     ([5000], 5000, 157),                # 256 slots: 32 rows each
     ([300, 290, 300], 300, 57),         # 86 slots each: 16 rows, 19 chunks for every length
     ([40, 3000], 3000, 96),             # 128 slots for the longest alone: 32 rows; from both lengths the same
-    ([100, 6400], 6400, 204),           # ... 64 rows; from both lengths 32
-], ids=["one65", "one5000", "even3", "skew3000", "skew6400"])
+    ([100, 6400], 6400, 102),           # ... 64 rows; 32 would be more than the 128 the merge takes at once
+    ([6400] + [100] * 4, 6400, 108),    # 52 slots for the longest alone: 128 rows; from all lengths 64
+    ([3000] + [10] * 39, 3000, 55),     # 512 rows; from all lengths 192: 16 chunks, what the merge takes at once
+    ([2900] * 40, 3000, 280),           # 7 slots each, also where that is more workgroups than CUs
+], ids=["one65", "one5000", "even3", "skew3000", "skew6400", "skew5", "skew40", "round40"])
 def test_decode_chunk_partials(lengths, cap_len, want):
     """How many partials the absorbed form makes (each is rounded to fp16, so
     fewer of them would cost precision): those of the longest length cut for
     the slots in half tiles, or of all lengths where they differ and that cuts
-    finer.  Counted in the caller's workspace, whose second part holds them."""
+    finer.  Counted in the caller's workspace, whose second part holds them.
+    (skew6400 had 204 chunks while the cut from all lengths had no bound for
+    the merge; the expected counts follow from the rule, not from a run.)"""
     t = H.torch()
     L = configs.LayerShape(d=256, n_q_heads=8, n_kv_heads=8, head_dim=64, r=128)
     ol, dl = _random_factor_layer(L, 1508)
